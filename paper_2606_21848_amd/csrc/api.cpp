@@ -429,7 +429,7 @@ int keyless_fold_routing(const void* W_Q, const void* W_R, int d_model, int H, i
   g.strideC = d_head;
   g.batch = H;
   g.dtype = dtype;
-  return hip_status(kl::launch_gemm_simple(g, static_cast<hipStream_t>(stream)),
+  return hip_status(kl::launch_gemm_f32(g, static_cast<hipStream_t>(stream)),
                     "keyless_fold_routing");
 }
 
@@ -662,7 +662,8 @@ int attend_entry(const char* who, const void* xa, const void* xb, const void* W_
     return attend_packed_core(who, xa, xb, packed, B, N_a, N_b, d_model, H, G, d_head, causal,
                               scale, out, qv.qr, qv.vv, st);
   }
-  // fp32: VALU kernels on the weights as given.
+  // fp32: the weights as given, both projections in one launch when they read
+  // the same tokens.
   const void* Wt = W_Q;
   if (W_R) {
     void* fold = w;
@@ -684,15 +685,23 @@ int attend_entry(const char* who, const void* xa, const void* xb, const void* W_
   g.C = qv.qr;
   g.N = NQ;
   g.ldb = g.ldc = NQ;
-  s = hip_status(kl::launch_gemm_simple(g, st), who);
-  if (s != KL_OK) return s;
-  g.A = xb;
-  g.M = B * N_b;
-  g.Bm = W_V;
-  g.C = qv.vv;
-  g.N = NV;
-  g.ldb = g.ldc = NV;
-  s = hip_status(kl::launch_gemm_simple(g, st), who);
+  const bool both = xa == xb && N_a == N_b;
+  if (both) {
+    g.B2 = W_V;
+    g.C2 = qv.vv;
+    g.N2 = NV;
+    g.ldb2 = g.ldc2 = NV;
+  }
+  s = hip_status(kl::launch_gemm_f32(g, st), who);
+  if (s == KL_OK && !both) {
+    g.A = xb;
+    g.M = B * N_b;
+    g.Bm = W_V;
+    g.C = qv.vv;
+    g.N = NV;
+    g.ldb = g.ldc = NV;
+    s = hip_status(kl::launch_gemm_f32(g, st), who);
+  }
   if (s != KL_OK || N_a == 0) return s;
   return run_attention(who, qv.qr, NQ, qv.vv, NV, out, B, N_a, N_b, H, G, d_head, causal, scale,
                        dtype, st);
@@ -926,29 +935,6 @@ int keyless_weight_gradients(const void* x, const void* W_Q, const void* W_R, co
   hipStream_t st = static_cast<hipStream_t>(stream);
   const long M = (long)B * N, NQ = (long)H * d_head, NV = (long)G * d_head;
   char* w = static_cast<char*>(ws);
-  auto gemm = [&](const void* A, long lda, long a_cs, const void* Bm, long ldb, long b_cs, void* C,
-                  long ldc, long Mm, long Nn, long Kk, int batch, long sA, long sB, long sC,
-                  int accumulate) {
-    kl::GemmParams g{};
-    g.A = A;
-    g.Bm = Bm;
-    g.C = C;
-    g.M = (int)Mm;
-    g.N = (int)Nn;
-    g.K = (int)Kk;
-    g.lda = lda;
-    g.a_cs = a_cs;
-    g.ldb = ldb;
-    g.b_cs = b_cs;
-    g.ldc = ldc;
-    g.batch = batch;
-    g.strideA = sA;
-    g.strideB = sB;
-    g.strideC = sC;
-    g.dtype = dtype;
-    g.accumulate = accumulate;
-    return hip_status(kl::launch_gemm_simple(g, st), who);
-  };
   const long dk = d_head;
   // bf16 with 16-byte aligned operands, head widths and d_model multiples of
   // 64: every product runs on the matrix cores, in the form above (each
@@ -1096,21 +1082,66 @@ int keyless_weight_gradients(const void* x, const void* W_Q, const void* W_R, co
   // K = 0 and write zero weight gradients; the token-shaped outputs are empty.
   void* Q = w;                                                   // X W^Q       [M, NQ]
   void* dQ = w + align256((size_t)M * NQ * elem_bytes(dtype));    // dQ~ W^R^T   [M, NQ]
+  auto product = [&](const void* A, long lda, long a_cs, const void* Bm, long ldb, long b_cs, void* C,
+                     long ldc, long rows, long cols, long K) {
+    kl::GemmParams g{};
+    g.A = A;
+    g.lda = lda;
+    g.a_cs = a_cs;
+    g.Bm = Bm;
+    g.ldb = ldb;
+    g.b_cs = b_cs;
+    g.C = C;
+    g.ldc = ldc;
+    g.M = (int)rows;
+    g.N = (int)cols;
+    g.K = (int)K;
+    g.batch = 1;
+    g.dtype = dtype;
+    return g;
+  };
+  auto per_head = [&](kl::GemmParams g, long sA, long sB, long sC) {
+    g.batch = H;
+    g.strideA = sA;
+    g.strideB = sB;
+    g.strideC = sC;
+    return g;
+  };
+  auto run = [&](const kl::GemmParams& g) { return hip_status(kl::launch_gemm_f32(g, st), who); };
   int s = KL_OK;
   // dQ_h = dQ~_h (W^R_h)^T: B(k, n) = W^R_h[n][k].
-  if (dW_Q || dx) s = gemm(dq_routed, NQ, 1, W_R, 1, dk, dQ, NQ, M, dk, dk, H, dk, dk * dk, dk, 0);
+  if (dW_Q || dx)
+    s = run(per_head(product(dq_routed, NQ, 1, W_R, 1, dk, dQ, NQ, M, dk, dk), dk, dk * dk, dk));
   // Eq. 5: dW^R_h = (X W^Q_h)^T dQ~_h, a contraction over the tokens.
   if (s == KL_OK && dW_R) {
-    s = gemm(x, d_model, 1, W_Q, NQ, 1, Q, NQ, M, NQ, d_model, 1, 0, 0, 0, 0);
-    if (s == KL_OK) s = gemm(Q, 1, NQ, dq_routed, NQ, 1, dW_R, dk, dk, dk, M, H, dk, dk, dk * dk, 0);
+    s = run(product(x, d_model, 1, W_Q, NQ, 1, Q, NQ, M, NQ, d_model));
+    if (s == KL_OK)
+      s = run(per_head(product(Q, 1, NQ, dq_routed, NQ, 1, dW_R, dk, dk, dk, M), dk, dk, dk * dk));
   }
-  // dW^Q = X^T dQ, and Eq. 6: dW^V = X^T dV (both of its terms are inside dV).
-  if (s == KL_OK && dW_Q) s = gemm(x, 1, d_model, dQ, NQ, 1, dW_Q, NQ, d_model, NQ, M, 1, 0, 0, 0, 0);
-  if (s == KL_OK && dW_V) s = gemm(x, 1, d_model, dv, NV, 1, dW_V, NV, d_model, NV, M, 1, 0, 0, 0, 0);
-  // dX = dQ (W^Q)^T + dV (W^V)^T.
+  // dW^Q = X^T dQ, and Eq. 6: dW^V = X^T dV (both of its terms are inside dV), in one launch.
+  if (s == KL_OK && (dW_Q || dW_V)) {
+    const bool q = dW_Q != nullptr;
+    kl::GemmParams g = product(x, 1, d_model, q ? dQ : dv, q ? NQ : NV, 1, q ? dW_Q : dW_V,
+                               q ? NQ : NV, d_model, q ? NQ : NV, M);
+    if (q && dW_V) {
+      g.B2 = dv;
+      g.ldb2 = NV;
+      g.C2 = dW_V;
+      g.ldc2 = NV;
+      g.N2 = (int)NV;
+    }
+    s = run(g);
+  }
+  // dX = dQ (W^Q)^T + dV (W^V)^T in one k loop.
   if (s == KL_OK && dx) {
-    s = gemm(dQ, NQ, 1, W_Q, 1, NQ, dx, d_model, M, d_model, NQ, 1, 0, 0, 0, 0);
-    if (s == KL_OK) s = gemm(dv, NV, 1, W_V, 1, NV, dx, d_model, M, d_model, NV, 1, 0, 0, 0, 1);
+    kl::GemmParams g = product(dQ, NQ, 1, W_Q, 1, NQ, dx, d_model, M, d_model, NQ);
+    g.A1 = dv;
+    g.lda1 = NV;
+    g.B1 = W_V;
+    g.ldb1 = 1;
+    g.b_cs1 = NV;
+    g.K1 = (int)NV;
+    s = run(g);
   }
   return s;
 }

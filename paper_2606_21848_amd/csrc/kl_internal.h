@@ -94,12 +94,12 @@ struct ProjectParams {
 bool project_supported(int K);
 hipError_t launch_project(const ProjectParams& p, hipStream_t stream);
 
-// C[b] (M x N) = A[b] (M x K) * B[b] (K x N), row-major with leading
-// dimensions, fp32 accumulation; batched by pointer strides. Generic tiled
-// kernel for the small products (routing fold, fp32 prefill projections).
-// C (M x N) = A (M x K) B (K x N) [+ C], fp32 arithmetic. Element (m, k) of A
-// is at m lda + k a_cs, element (k, n) of B at k ldb + n b_cs (a_cs, b_cs of 0
-// mean 1), so transposed operands are a choice of strides.
+// C[b] (M x N) = A[b] (M x K) B[b] (K x N) [+ A1 B1] [+ C], fp32 arithmetic on
+// fp32 or bf16 elements, row-major C. Element (m, k) of A is at m lda + k a_cs,
+// element (k, n) of B at k ldb + n b_cs (a_cs, b_cs of 0 mean 1), so transposed
+// operands are a choice of strides; no alignment is needed. Optional: a second
+// term over K1 (strides of the same kind), and a second column block
+// C2 (M x N2) = A B2 in the same launch.
 struct GemmParams {
   const void* A; const void* Bm; void* C;
   int M, N, K;
@@ -108,10 +108,15 @@ struct GemmParams {
   int batch;
   kl_dtype dtype;
   long a_cs, b_cs;
-  int accumulate;                  // nonzero: C += A B
+  const void* A1; const void* B1;  // second term, K1 = 0 for none
+  int K1;
+  long lda1, ldb1, b_cs1;          // its A has the column stride a_cs
+  const void* B2; void* C2;        // second column block, N2 = 0 for none
+  int N2;
+  long ldb2, ldc2;
 };
 
-hipError_t launch_gemm_simple(const GemmParams& p, hipStream_t stream);
+hipError_t launch_gemm_f32(const GemmParams& p, hipStream_t stream);
 
 // bf16 MFMA GEMM: C (M x N) = A0 W0^T + A1 W1^T with A0 [M, K0], W0 [N, K0],
 // A1 [M, K1], W1 [N, K1] (K contiguous in all four; K1 = 0 drops the second
@@ -227,7 +232,7 @@ hipError_t launch_attention_backward(const BwdParams& p, hipStream_t stream);
 // bf16 MFMA flash-style keyless attention (d_head 64 or 128).
 bool attn_bf16_supported(const AttnParams& p);
 hipError_t launch_prefill_attention(const AttnParams& p, hipStream_t stream);
-// fp32 (or fallback) VALU attention.
+// VALU attention for what the kernels above do not take.
 hipError_t launch_prefill_attention_simple(const AttnParams& p, hipStream_t stream);
 
 // Measuring kernels (not part of the method): a streaming read of bytes (a
