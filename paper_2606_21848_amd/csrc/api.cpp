@@ -542,6 +542,7 @@ int run_attention(const char* who, const void* qr, long q_stride, const void* vv
   // No value rows (an empty X^(b)): the VALU kernel writes the zero rows.
   if (Nk > 0 && kl::attn_bf16_supported(a))
     return hip_status(kl::launch_prefill_attention(a, st), who);
+  if (kl::attn_f32_supported(a)) return hip_status(kl::launch_attention_f32(a, st), who);
   return hip_status(kl::launch_prefill_attention_simple(a, st), who);
 }
 

@@ -17,16 +17,16 @@
 // output would put that rounding into every dP - Dd) and then bwd_dv_kernel
 // (one workgroup per 192-row value tile and value group; query and dO tiles of
 // every head of the group stream through LDS, the values stay in registers).
-// fp32 (and shapes the matrix-core kernels do not take): bwd_prep_kernel (Dd
-// from the fp32 output, else from the output) and two vector-ALU kernels. No
+// fp32 has matrix-core kernels of its own (attn_f32.hip); what none of them
+// takes: bwd_prep_kernel (Dd from the fp32 output, else from the output) and
+// two vector-ALU kernels. No
 // atomics: every output element is written once, by one lane.
 //
 // bf16 runs on v_mfma_f32_16x16x32_bf16 with the forward's operand layouts:
 // scores come out with one query per lane (S^T = V Q~^T) in the dQ~ kernel and
 // one value row per lane (S = Q~ V^T) in the dV kernel, and in both the weights
 // feed the next product as its B operand without a transpose; the transposed
-// A operands come from ds_read_b64_tr_b16 on the row-major tiles. fp32 runs
-// VALU kernels of the same structure.
+// A operands come from ds_read_b64_tr_b16 on the row-major tiles.
 
 #include <type_traits>
 
@@ -641,7 +641,7 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_dv_kernel(BwdParams p) {
 }
 
 // ---------------------------------------------------------------------------
-// fp32 (and any dtype): VALU, one thread per query row (dQ~) or value row (dV)
+// Vector ALU, one thread per query row (dQ~) or value row (dV)
 // ---------------------------------------------------------------------------
 
 template <typename T, int D>
@@ -815,6 +815,7 @@ hipError_t launch_attention_backward(const BwdParams& p, hipStream_t st) {
   // kernel's prologue, which publishes it for the dV kernel), else from P and
   // dP in the dQ~ kernel's first sweep; on the vector ALU from the output (the
   // prep kernel).
+  if (attn_bwd_f32_supported(p)) return launch_attention_backward_f32(p, st);
   const bool mfma = attn_bwd_mfma_supported(p);
   if (!mfma) {
     hipError_t e = p.dtype == KL_BF16 ? launch_prep<uint16_t>(p, st) : launch_prep<float>(p, st);

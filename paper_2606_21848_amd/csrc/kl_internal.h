@@ -232,6 +232,12 @@ hipError_t launch_attention_backward(const BwdParams& p, hipStream_t stream);
 // bf16 MFMA flash-style keyless attention (d_head 64 or 128).
 bool attn_bf16_supported(const AttnParams& p);
 hipError_t launch_prefill_attention(const AttnParams& p, hipStream_t stream);
+// fp32 MFMA attention (d_head 64 or 128, 16-byte aligned operands, at least one
+// value row) and its backward.
+bool attn_f32_supported(const AttnParams& p);
+hipError_t launch_attention_f32(const AttnParams& p, hipStream_t stream);
+bool attn_bwd_f32_supported(const BwdParams& p);
+hipError_t launch_attention_backward_f32(const BwdParams& p, hipStream_t stream);
 // VALU attention for what the kernels above do not take.
 hipError_t launch_prefill_attention_simple(const AttnParams& p, hipStream_t stream);
 

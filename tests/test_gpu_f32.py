@@ -2,12 +2,13 @@
 fp32 attention forward and backward) at the edges of their tiles and in every
 way they load an operand, against the CPU oracle."""
 
+import numpy as np
 import pytest
 import torch
 
 from oracle import keyless as K
 from paper_2606_21848_amd import binding as kb
-from tests.parity import assert_parity, say, to64
+from tests.parity import assert_parity, rowwise_rel, say, to64
 from workloads import synth
 
 pytestmark = pytest.mark.gpu
@@ -67,3 +68,47 @@ def test_layer_f32(lib, N, d, H, G, dk, shift):
                                          to64(dv), H, G, dk)
     for name, g in grads.items():
         assert_parity(g, ref[name], F32, name, 1e-2)
+
+
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("B,N,H,G,dk", [(1, 15, 2, 2, 64), (2, 16, 4, 2, 128), (1, 17, 3, 1, 128),
+                                        (1, 129, 2, 2, 128), (2, 250, 4, 1, 64)])
+def test_attention_f32(lib, causal, B, N, H, G, dk):
+    """Whole and ragged 16-row blocks, fewer and more of them than waves."""
+    say(f"fp32 attention B={B} N={N} H={H} G={G} dk={dk} causal={causal}")
+    q, v, g = (synth.normal((B, N, n, dk), 33, i, 1.0, F32) for i, n in enumerate((H, G, H)))
+    o32 = torch.empty((B, N, H, dk), dtype=F32, device=DEV)
+    out, lse = kb.keyless_attention_forward(q.to(DEV), v.to(DEV), causal=causal, out_f32=o32)
+    dq, dv = kb.keyless_attention_backward(q.to(DEV), v.to(DEV), out, g.to(DEV), lse, causal=causal)
+    torch.cuda.synchronize()
+    assert torch.equal(out, o32)
+    ref_lse = K.attention_logsumexp(to64(q), to64(v), H, G, dk, causal=causal)
+    assert rowwise_rel(lse, ref_lse) <= 1e-4
+    rq, rv = K.keyless_attention_backward(to64(q), to64(v), to64(g), H, G, dk, causal=causal)
+    scale = 1e-2 * max(np.abs(rq).max(), np.abs(rv).max())
+    assert_parity(dq, rq, F32, "dQ~", 1e-2, scale)
+    assert_parity(dv, rv, F32, "dV", 1e-2, scale)
+
+
+def test_unseen_rows_do_not_reach_a_row_f32(lib):
+    """Causal rows before an infinite value row, and value rows after a query row
+    with a NaN gradient, get the bits that they get without it."""
+    N, H, dk = 40, 2, 64
+    say("fp32 attention, non-finite rows out of sight")
+    q, v, g = (synth.normal((1, N, H, dk), 34, i, 1.0, F32).to(DEV) for i in range(3))
+    out, lse = kb.keyless_attention_forward(q, v)
+    dq, dv = kb.keyless_attention_backward(q, v, out, g, lse)
+    at = 21  # inside the second block
+    v2, g2 = v.clone(), g.clone()
+    v2[:, at, :, 5] = float("inf")
+    g2[:, at, :, 7] = float("nan")
+    out2, lse2 = kb.keyless_attention_forward(q, v2)
+    dq2, _ = kb.keyless_attention_backward(q, v2, out, g, lse)
+    _, dv3 = kb.keyless_attention_backward(q, v, out, g2, lse)
+    torch.cuda.synchronize()
+    for a, b in ((out2, out), (dq2, dq)):
+        torch.testing.assert_close(a[:, :at], b[:, :at], rtol=1e-5, atol=1e-6)
+    torch.testing.assert_close(lse2[:, :, :at], lse[:, :, :at], rtol=1e-6, atol=1e-6)
+    torch.testing.assert_close(dv3[:, at + 1:], dv[:, at + 1:], rtol=1e-5, atol=1e-6)
+    assert not torch.isfinite(out2[:, at:, :, 5]).any()
+    assert torch.isnan(dv3[:, :at + 1, :, 7]).all()
