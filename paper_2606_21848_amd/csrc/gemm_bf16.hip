@@ -10,18 +10,24 @@
 // values). fp32 accumulation in v_mfma_f32_16x16x32_bf16, one rounding to
 // bf16 on store.
 //
-// Tile 256 x 256 x 64, 16 waves (4 x 4), each wave 64 x 64 of C (64 fp32
-// accumulators per lane, four waves per SIMD: while some waves restart a k-tile
-// with their LDS reads after the barrier, others keep the matrix pipe busy). Each operand tile is 256 rows of
-// 128 bytes in LDS with the 16-byte chunks of row r XOR-swizzled by
-// (r >> 1) & 7, so the fragment reads (16 rows per access) are free of bank
-// conflicts. Tiles move from memory straight into LDS (global_load_lds, 16
-// bytes per lane, no register staging); the swizzle is applied to the global
-// addresses. Two LDS stages (128 KiB): the next tile is in flight while the
-// current one is multiplied.
+// Large products: tile 256 x 256 x 64, 16 waves (4 x 4), each wave 64 x 64 of C
+// (64 fp32 accumulators per lane, four waves per SIMD: while some waves restart a
+// k-tile with their LDS reads after the barrier, others keep the matrix pipe
+// busy). Each operand tile is rows of 128 bytes in LDS with the 16-byte chunks of
+// row r XOR-swizzled by (r >> 1) & 7, so the fragment reads (16 rows per access)
+// are free of bank conflicts. Tiles move from memory straight into LDS
+// (global_load_lds, 16 bytes per lane, no register staging); the swizzle is
+// applied to the global addresses. Two LDS stages (128 KiB): the next tile is in
+// flight while the current one is multiplied.
+// A product with few such tiles leaves most CUs idle (a prompt of 517 tokens at
+// N 1792: 21 tiles for 256 CUs), and what bounds it is the latency of its k-steps
+// (0.4 us each whatever their size), so it takes 128 x 128 or 64 x 64 tiles: more
+// workgroups, shorter steps, and a third stage where one CU holds few waves. The
+// rule and its measurements stand at launch_gemm_bf16.
 // Workgroup ids are remapped so each XCD owns a band of tile rows walked
 // column-major, which keeps concurrently running tiles in that XCD's L2.
 
+#include <cmath>
 #include <type_traits>
 
 #include "kl_device.h"
@@ -34,10 +40,26 @@ typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8_t;
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4_t;
 typedef __attribute__((address_space(3))) unsigned char lds_u8;
 
-constexpr int BM = 256, BN = 256, BK = 64;
-constexpr int kThreads = 1024;
-constexpr int TILE_BYTES = 256 * BK * 2;  // one operand tile, 32 KiB
+constexpr int BK = 64;
 static_assert(BK == 64, "the fragment schedule assumes two 32-wide k-steps per tile");
+
+// An output tile of BM x BN on WM x WN waves, ST stages of LDS.
+template <int BM_, int BN_, int WM_, int WN_, int ST_>
+struct Shape {
+  static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_, ST = ST_;
+  static constexpr int WAVES = WM * WN, THREADS = WAVES * 64;
+  static constexpr int TA = BM * BK * 2, TW = BN * BK * 2;  // bytes of an operand tile
+  static constexpr int STAGE = TA + TW, LDS = ST * STAGE;
+  static constexpr int CA = BM / 8 / WAVES;  // copies per wave and operand tile
+  static constexpr int RM = BM / WM / 16, RN = BN / WN / 16;      // 16-wide blocks per wave
+  static constexpr int EU = WAVES >= 8 ? 4 : 2;                   // waves per SIMD to fit
+  static_assert(ST == 2 || ST == 3, "the loop's waits");
+  static_assert(CA * 8 * WAVES == BM && BM == BN, "whole copies per wave");
+};
+using Shape256 = Shape<256, 256, 4, 4, 2>;  // one workgroup per CU
+using Shape128 = Shape<128, 128, 2, 2, 2>;  // two
+using Shape128Deep = Shape<128, 128, 2, 4, 3>;  // one: 8 waves, two k-tiles in flight
+using Shape64 = Shape<64, 64, 2, 2, 3>;     // three
 
 struct GemmParams2 {
   const uint16_t* A0;  // [M, K0], row stride lda0 (elements)
@@ -63,9 +85,10 @@ __device__ __forceinline__ int swz(int row, int chunk) {
 // TWO: the second term is present (one more pair of copy offsets per lane and
 // a uniform choice per k-tile; the projections take the plain form). F32: the
 // outputs are stored in fp32 (partial products of a split contraction).
-template <bool TWO, bool F32>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 4)))
+template <class SH, bool TWO, bool F32>
+__global__ __launch_bounds__(SH::THREADS) __attribute__((amdgpu_waves_per_eu(SH::EU, 4)))
 void gemm_bf16_kernel(GemmParams2 p) {
+  constexpr int BM = SH::BM, BN = SH::BN, RM = SH::RM, RN = SH::RN, ST = SH::ST;
   using CT = std::conditional_t<F32, float, uint16_t>;
   const int tilesM = (p.M + BM - 1) / BM, tilesN = (p.N + BN - 1) / BN;
   const int ntiles = tilesM * tilesN;
@@ -78,8 +101,9 @@ void gemm_bf16_kernel(GemmParams2 p) {
     C1 += (size_t)blockIdx.y * p.sC1 + (size_t)blockIdx.z * p.zC0;
   }
   int wg = blockIdx.x;
-  // XCD-aware order: hardware places workgroup i on XCD i % 8.
-  if ((ntiles & 7) == 0) wg = (wg & 7) * (ntiles >> 3) + (wg >> 3);
+  // XCD-aware order: hardware places workgroup i on XCD i % 8; each XCD takes a
+  // contiguous run of tiles.
+  wg = (wg & 7) * (ntiles >> 3) + min(wg & 7, ntiles & 7) + (wg >> 3);
   constexpr int GM = 4;
   const int group = wg / (GM * tilesN);
   const int first_m = group * GM;
@@ -88,32 +112,32 @@ void gemm_bf16_kernel(GemmParams2 p) {
   const int m0 = (first_m + in_group % gsize) * BM;
   const int n0 = (in_group / gsize) * BN;
 
-  // Two pipeline stages, each an A tile and a W tile: [stage][A | W].
+  // ST pipeline stages, each an A tile and a W tile: [stage][A | W].
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
 
   const int t = threadIdx.x, lane = t & 63;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
-  const int wm = wave >> 2, wn = wave & 3;  // wave tile: rows 64 wm.., columns 64 wn..
+  const int wm = wave / SH::WN, wn = wave % SH::WN;  // wave tile: rows 16 RM wm.., columns 16 RN wn..
 
   // Direct-to-LDS copies: one wave instruction fills 8 rows (1 KiB) of a tile,
   // lane L landing at byte 16 L, i.e. row L / 8, physical chunk L % 8, which
-  // holds logical chunk (L % 8) ^ ((row >> 1) & 7). Each wave fills 2 row groups
+  // holds logical chunk (L % 8) ^ ((row >> 1) & 7). Each wave fills CA row groups
   // of each operand. Rows past the end are clamped: they only feed output rows
   // or columns that are never stored. Per-lane byte offsets for each term.
   constexpr int NT = TWO ? 2 : 1;
-  uint32_t offA[NT][2], offW[NT][2];  // [term][row group]
+  uint32_t offA[NT][SH::CA], offW[NT][SH::CA];  // [term][row group]
+  auto lane_offsets = [&](auto& off, int row0, int rows, long ld0, long ld1) {
 #pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const int r = (i * 16 + wave) * 8 + (lane >> 3);
-    const int lc = (lane & 7) ^ ((r >> 1) & 7);
-    const int ra = min(m0 + r, p.M - 1), rw = min(n0 + r, p.N - 1);
-    offA[0][i] = (uint32_t)(((size_t)ra * p.lda0 + lc * 8) * 2);
-    offW[0][i] = (uint32_t)(((size_t)rw * p.ldw0 + lc * 8) * 2);
-    if constexpr (TWO) {
-      offA[NT - 1][i] = (uint32_t)(((size_t)ra * p.lda1 + lc * 8) * 2);
-      offW[NT - 1][i] = (uint32_t)(((size_t)rw * p.ldw1 + lc * 8) * 2);
+    for (int i = 0; i < SH::CA; ++i) {
+      const int r = (i * SH::WAVES + wave) * 8 + (lane >> 3);
+      const int lc = (lane & 7) ^ ((r >> 1) & 7);
+      const int rc = min(row0 + r, rows - 1);
+      off[0][i] = (uint32_t)(((size_t)rc * ld0 + lc * 8) * 2);
+      if constexpr (TWO) off[NT - 1][i] = (uint32_t)(((size_t)rc * ld1 + lc * 8) * 2);
     }
-  }
+  };
+  lane_offsets(offA, m0, p.M, p.lda0, p.lda1);
+  lane_offsets(offW, n0, p.N, p.ldw0, p.ldw1);
   const int nk0 = p.K0 / BK;  // k-tiles of the first term
   // Copies of k-tile kt (of the concatenated k range) into one stage.
   auto issue = [&](lds_u8* sa, lds_u8* sw, int kt) {
@@ -122,65 +146,73 @@ void gemm_bf16_kernel(GemmParams2 p) {
     const unsigned char* ga = reinterpret_cast<const unsigned char*>(second ? p.A1 : p.A0) + (size_t)k0 * 2;
     const unsigned char* gw = reinterpret_cast<const unsigned char*>(second ? p.W1 : p.W0) + (size_t)k0 * 2;
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const uint32_t grp_off = (uint32_t)((i * 16 + wave) * 1024);
+    for (int i = 0; i < SH::CA; ++i) {
+      const uint32_t grp_off = (uint32_t)((i * SH::WAVES + wave) * 1024);
       copy_to_lds(ga, second ? offA[NT - 1][i] : offA[0][i], (uint32_t)(uintptr_t)sa + grp_off);
       copy_to_lds(gw, second ? offW[NT - 1][i] : offW[0][i], (uint32_t)(uintptr_t)sw + grp_off);
     }
   };
 
-  f32x4_t acc[4][4];
+  f32x4_t acc[RM][RN];
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < RM; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    for (int j = 0; j < RN; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
   const int fr = lane & 15, grp = lane >> 4;
-  // Per 32-wide k-step: the wave's 4 A and 4 W fragments, then its 16 products
-  // (one fragment set; the other three waves on the SIMD cover the read latency).
+  // Per 32-wide k-step: the wave's RM A and RN W fragments, then their products
+  // (one fragment set; the other waves on the SIMD cover the read latency).
   auto compute = [&](const lds_u8* a, const lds_u8* w) {
 #pragma unroll
     for (int ks = 0; ks < BK / 32; ++ks) {
       const int chunk = ks * 4 + grp;
-      bf16x8_t af[4], bf[4];
+      bf16x8_t af[RM], bf[RN];
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
+      for (int i = 0; i < RM; ++i)
         af[i] = *reinterpret_cast<const __attribute__((address_space(3))) bf16x8_t*>(
-            a + swz(wm * 64 + i * 16 + fr, chunk));
+            a + swz(wm * (RM * 16) + i * 16 + fr, chunk));
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
+      for (int j = 0; j < RN; ++j)
         bf[j] = *reinterpret_cast<const __attribute__((address_space(3))) bf16x8_t*>(
-            w + swz(wn * 64 + j * 16 + fr, chunk));
+            w + swz(wn * (RN * 16) + j * 16 + fr, chunk));
       // W as the A operand: the result block is C^T, so a lane holds four
       // consecutive output columns of one row (one 8-byte store in bf16).
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
+      for (int i = 0; i < RM; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
+        for (int j = 0; j < RN; ++j)
           acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bf[j], af[i], acc[i][j], 0, 0, 0);
     }
   };
 
   lds_u8* const base = (lds_u8*)smem;
-  auto stageA = [&](int st) { return base + st * 2 * TILE_BYTES; };
-  auto stageW = [&](int st) { return base + st * 2 * TILE_BYTES + TILE_BYTES; };
+  auto stageA = [&](int st) { return base + st * SH::STAGE; };
+  auto stageW = [&](int st) { return base + st * SH::STAGE + SH::TA; };
   const int nk = TWO ? nk0 + p.K1 / BK : nk0;
-  issue(stageA(0), stageW(0), 0);
+#pragma unroll
+  for (int i = 0; i < ST - 1; ++i)
+    if (i < nk) issue(stageA(i), stageW(i), i);
   // One barrier per k-tile. Before it, each wave waits for its copies of tile
-  // kt (the only ones in flight) and for its own LDS reads of tile kt - 1 (the
-  // barrier does not wait for those); after it, both hold for every wave, so
-  // the copies of tile kt + 1 may refill the stage of tile kt - 1 while tile kt
-  // is multiplied.
+  // kt (those of the later tiles may stay in flight) and for its own LDS reads
+  // of tile kt - 1 (the barrier does not wait for those); after it, both hold
+  // for every wave, so the copies of tile kt + ST - 1 may refill the stage of
+  // tile kt - 1 while tile kt is multiplied.
+  constexpr int PER = 2 * SH::CA;
+  int ring = 0;
   for (int kt = 0; kt < nk; ++kt) {
-    const int cur = kt & 1;
-    KL_WAIT_VMCNT(0);
+    const int ahead = nk - 1 - kt;  // tiles after kt, of which ST - 2 may be in flight
+    if (ST == 3 && ahead >= 1) KL_WAIT_VMCNT(PER);
+    else KL_WAIT_VMCNT(0);
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     __syncthreads();
-    if (kt + 1 < nk) issue(stageA(cur ^ 1), stageW(cur ^ 1), kt + 1);
+    const int cur = ST == 2 ? kt & 1 : ring;
+    const int refill = ST == 2 ? cur ^ 1 : (cur == 0 ? ST - 1 : cur - 1);
+    if (kt + ST - 1 < nk) issue(stageA(refill), stageW(refill), kt + ST - 1);
     compute(stageA(cur), stageW(cur));
+    ring = cur == ST - 1 ? 0 : cur + 1;
   }
 
-  // Lane holds C[row 16 i + fr][col 16 j + 4 grp + r] of the wave's 64 x 64 block:
+  // Lane holds C[row 16 i + fr][col 16 j + 4 grp + r] of the wave's block:
   // four consecutive columns, stored as one 8-byte (bf16) or 16-byte (fp32)
   // store when they lie on one side of n_split, inside N, and the outputs' row
   // strides and bases keep them aligned (uniform); otherwise element by element.
@@ -192,12 +224,12 @@ void gemm_bf16_kernel(GemmParams2 p) {
   auto store = [&](auto check_rows) {
     constexpr bool CHECK = decltype(check_rows)::value;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int row = m0 + wm * 64 + i * 16 + fr;
+    for (int i = 0; i < RM; ++i) {
+      const int row = m0 + wm * (RM * 16) + i * 16 + fr;
       if (CHECK && row >= p.M) continue;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int col = n0 + wn * 64 + j * 16 + grp * 4;
+      for (int j = 0; j < RN; ++j) {
+        const int col = n0 + wn * (RN * 16) + j * 16 + grp * 4;
         if (vec && col + 4 <= p.N && (col + 4 <= p.n_split || col >= p.n_split)) {
           CT* dst = col < p.n_split ? C0 + (size_t)row * p.ldc0 + col
                                     : C1 + (size_t)row * p.ldc1 + (col - p.n_split);
@@ -267,18 +299,29 @@ const char* gemm_bf16_unsupported(int M, int N, int K, long lda, long ldc0, long
   return why;
 }
 
-constexpr size_t kGemmLds = 4 * TILE_BYTES;
+namespace {
+
+template <class SH, bool TWO, bool F32>
+hipError_t launch_shape(const GemmParams2& p, int batch, int zbatch, hipStream_t st) {
+  static std::atomic<uint32_t> done{0};
+  hipError_t e = set_max_lds((const void*)gemm_bf16_kernel<SH, TWO, F32>, SH::LDS, done);
+  if (e != hipSuccess) return e;
+  const int tiles = ((p.M + SH::BM - 1) / SH::BM) * ((p.N + SH::BN - 1) / SH::BN);
+  hipLaunchKernelGGL((gemm_bf16_kernel<SH, TWO, F32>), dim3(tiles, batch, zbatch), dim3(SH::THREADS),
+                     SH::LDS, st, p);
+  return hipGetLastError();
+}
+
+template <class SH>
+hipError_t launch_form(const GemmParams2& p, int batch, int zbatch, bool f32, hipStream_t st) {
+  if (p.K1 > 0) return launch_shape<SH, true, false>(p, batch, zbatch, st);
+  return f32 ? launch_shape<SH, false, true>(p, batch, zbatch, st)
+             : launch_shape<SH, false, false>(p, batch, zbatch, st);
+}
+
+}  // namespace
 
 hipError_t launch_gemm_bf16(const GemmBf16Args& a, hipStream_t st) {
-  static std::atomic<uint32_t> attr_one{0}, attr_two{0}, attr_f32{0};
-  const void* kern = a.K1 > 0 ? (const void*)gemm_bf16_kernel<true, false>
-                   : a.c_f32  ? (const void*)gemm_bf16_kernel<false, true>
-                              : (const void*)gemm_bf16_kernel<false, false>;
-  {
-    hipError_t e = set_max_lds(kern, (int)kGemmLds,
-                               a.K1 > 0 ? attr_two : (a.c_f32 ? attr_f32 : attr_one));
-    if (e != hipSuccess) return e;
-  }
   GemmParams2 p{};
   p.A0 = static_cast<const uint16_t*>(a.A0);
   p.W0 = static_cast<const uint16_t*>(a.W0);
@@ -304,15 +347,28 @@ hipError_t launch_gemm_bf16(const GemmBf16Args& a, hipStream_t st) {
   p.zA0 = a.zA0;
   p.zW0 = a.zW0;
   p.zC0 = a.zC0;
-  const int tiles = ((a.M + BM - 1) / BM) * ((a.N + BN - 1) / BN);
-  const dim3 grid(tiles, a.batch > 1 ? a.batch : 1, a.zbatch > 1 ? a.zbatch : 1);
-  if (a.K1 > 0)
-    hipLaunchKernelGGL((gemm_bf16_kernel<true, false>), grid, dim3(kThreads), kGemmLds, st, p);
-  else if (a.c_f32)
-    hipLaunchKernelGGL((gemm_bf16_kernel<false, true>), grid, dim3(kThreads), kGemmLds, st, p);
-  else
-    hipLaunchKernelGGL((gemm_bf16_kernel<false, false>), grid, dim3(kThreads), kGemmLds, st, p);
-  return hipGetLastError();
+  const int batch = a.batch > 1 ? a.batch : 1, zbatch = a.zbatch > 1 ? a.zbatch : 1;
+  auto tiles = [&](int T) {
+    return (double)((a.M + T - 1) / T) * ((a.N + T - 1) / T) * batch * zbatch;
+  };
+  // The shape whose workgroups take the least time, from the time of one k-step
+  // (64 deep) measured at K 1024 to 4096, in us: 256 x 256 tiles 1.7 per full
+  // round of 256 (one per CU), 1.3 for a last round that is partly empty; 128 x
+  // 128 tiles 0.95 per round of 512 (two per CU) or 0.65 for a last one of at
+  // most 256; 64 x 64 tiles 0.15 + 0.22 per 256. At N 1792, K 1536 (256 / 128 /
+  // 64, us): M 517: 37 / 18 / 9.3; M 2000: 38 / 17 / 23; M 4096: 40 / 28 / 41;
+  // at N = 8192, K = 4096: M 1000: 83 / 62 / 100, M 8192: 422 / 470 / 778.
+  auto rounds = [](double t, double per, double full, double part, double few) {
+    const double whole = std::floor(t / per), rest = t - whole * per;
+    return whole * full + (rest == 0 ? 0. : (2 * rest <= per ? few : part));
+  };
+  const double t256 = rounds(tiles(256), 256, 1.7, 1.3, 1.3);
+  const double t128 = rounds(tiles(128), 512, 0.95, 0.95, 0.65);
+  const double t64 = 0.15 + 0.22 * tiles(64) / 256;
+  if (t64 < t128 && t64 < t256) return launch_form<Shape64>(p, batch, zbatch, a.c_f32, st);
+  if (t256 <= t128) return launch_form<Shape256>(p, batch, zbatch, a.c_f32, st);
+  if (tiles(128) <= 256) return launch_form<Shape128Deep>(p, batch, zbatch, a.c_f32, st);
+  return launch_form<Shape128>(p, batch, zbatch, a.c_f32, st);
 }
 
 namespace {

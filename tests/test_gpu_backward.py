@@ -162,6 +162,21 @@ def test_weight_gradients_match_oracle(lib, dtype, B, N, d, H, G, dk):
     assert_parity(grads["dX"], ref["dX"], dtype, "dX", FLOOR)
 
 
+def test_weight_gradients_128_wide_tiles(lib):
+    """Products whose outputs take the 128-wide GEMM tiles (one term, two terms)."""
+    B, N, d, H, G, dk = 2, 901, 1472, 22, 2, 64
+    say("weight gradients, 128-wide tiles")
+    x, dq, dv = (synth.normal(s, 93, i) for i, s in enumerate(((B, N, d), (B, N, H, dk), (B, N, G, dk))))
+    W_Q = synth.normal((d, H * dk), 93, 4, d ** -0.5)
+    W_R = synth.normal((H, dk, dk), 93, 5, dk ** -0.5)
+    W_V = synth.normal((d, G * dk), 93, 6, d ** -0.5)
+    got = kb.keyless_weight_gradients(*(t.to(DEV) for t in (x, W_Q, W_R, W_V, dq, dv)), H, G)
+    torch.cuda.synchronize()
+    ref = K.keyless_projection_gradients(*(to64(t) for t in (x, W_Q, W_R, W_V, dq, dv)), H, G, dk)
+    for name, g in got.items():
+        assert_parity(g, ref[name], torch.bfloat16, name, FLOOR)
+
+
 @pytest.mark.parametrize("wanted", [("dW_Q",), ("dW_V",), ("dW_R",), ("dX",), ("dW_Q", "dX"),
                                     ("dW_R", "dW_V")])
 def test_weight_gradients_subsets(lib, wanted):

@@ -110,6 +110,23 @@ def test_prefill_matches_oracle(lib, dtype, causal, N, d, H, G, dk):
     assert_parity(out, O, dtype, "output")
 
 
+@pytest.mark.parametrize("d", [64, 128, 192, 256])
+@pytest.mark.parametrize("N,H,G", [(63, 4, 2), (1001, 26, 2), (2040, 28, 14), (2100, 64, 32)])
+def test_projection_tile_shapes(lib, N, H, G, d):
+    """The projection on each output tile (64 wide; 128 wide, one and two
+    workgroups per CU; 256 wide) with one to four k-tiles and ragged rows."""
+    say(f"projection N={N} H={H} G={G} d={d}")
+    B, dk = 2, 64
+    x = synth.normal((B, N, d), 25, 1)
+    W_Q = synth.normal((d, H * dk), 25, 2, d ** -0.5)
+    W_V = synth.normal((d, G * dk), 25, 4, d ** -0.5)
+    packed = kb.keyless_pack_weights(W_Q.to(DEV), None, W_V.to(DEV), H, G)
+    _, q, v = kb.keyless_prefill_packed(x.to(DEV), packed, H, G, return_qv=True)
+    torch.cuda.synchronize()
+    assert_parity(q.reshape(B, N, -1), to64(x) @ to64(W_Q), torch.bfloat16, "q")
+    assert_parity(v.reshape(B, N, -1), to64(x) @ to64(W_V), torch.bfloat16, "v")
+
+
 def test_tiny_fp32_layer_prefill_append_decode(lib):
     """One fp32 attention layer (d_model 256, 4 heads x 64): causal prefill of 128
     tokens, append the 128 values, decode with the last routed query over the
