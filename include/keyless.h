@@ -255,8 +255,10 @@ int keyless_attention_forward(const void* q_routed, const void* v, int B, int N,
  *   and dP in an extra sweep over the values (rowsum(dO * O) over the bf16
  *   output would carry its rounding into every dP - rowsum);
  *   dq_routed [B, N, H, d_head], dv [B, N, G, d_head]; all 16-byte aligned.
- *   ws, ws_bytes  keyless_attention_backward_workspace_size(B, N, H) bytes (the
- *                 per-row rowsum(dO * O), B*H*N floats)
+ *   ws, ws_bytes  keyless_attention_backward_workspace_size(B, N, H) bytes: the
+ *                 per-row rowsum(dO * O), B*H*N floats rounded up to 256 bytes
+ *                 (the least that is accepted), and room for fp32 partial sums
+ *                 of dv, which let bf16 calls with few value tiles fill the chip
  * Self-attention only (the value rows are the query rows). bf16 with d_head 64
  * or 128 runs on MFMA (P and dS rounded to bf16 for the products, fp32
  * accumulation); fp32 on the vector ALU. Every output element is written once

@@ -831,9 +831,24 @@ int keyless_attention_forward(const void* q_routed, const void* v, int B, int N,
                        d_head, causal, scale, dtype, static_cast<hipStream_t>(stream), lse, out_f32);
 }
 
+namespace {
+
+// The row sums that every call needs, and the most that the partial sums of dV
+// take for some G and d_head (a workspace without room for them is accepted).
+size_t bwd_rows_bytes(int B, int N, int H) { return align256((size_t)B * H * N * sizeof(float)); }
+size_t bwd_part_bytes(int B, int N, int H, int G, int d_head) {
+  const int S = kl::attn_bwd_splits(B, N, H, G);
+  return S > 1 ? (size_t)S * B * N * G * d_head * sizeof(float) : 0;
+}
+
+}  // namespace
+
 size_t keyless_attention_backward_workspace_size(int B, int N, int H) {
   if (B < 0 || N < 0 || H <= 0) return 0;
-  return align256((size_t)B * H * N * sizeof(float));
+  size_t part = 0;
+  for (int G = 1; G <= H; ++G)
+    if (H % G == 0) part = std::max(part, bwd_part_bytes(B, N, H, G, 128));
+  return bwd_rows_bytes(B, N, H) + align256(part);
 }
 
 int keyless_attention_backward(const void* q_routed, const void* v, const void* out,
@@ -849,7 +864,7 @@ int keyless_attention_backward(const void* q_routed, const void* v, const void* 
   if (!aligned16(q_routed) || !aligned16(v) || !aligned16(out) || !aligned16(dout) ||
       !aligned16(dq_routed) || !aligned16(dv))
     return fail(KL_ERR_INVALID_ARG, "%s: tensors must be 16-byte aligned", who);
-  const size_t need = keyless_attention_backward_workspace_size(B, N, H);
+  const size_t need = bwd_rows_bytes(B, N, H);
   if (need && (!ws || ws_bytes < need))
     return fail(KL_ERR_WORKSPACE, "%s: workspace of %zu bytes needed, %zu given", who, need, ws_bytes);
   if (B == 0 || N == 0) return KL_OK;
@@ -874,6 +889,12 @@ int keyless_attention_backward(const void* q_routed, const void* v, const void* 
   p.scale = scale_or_default(scale, d_head);
   p.scale_log2 = p.scale * kLog2e;
   p.dtype = dtype;
+  p.S = 1;
+  const size_t part = bwd_part_bytes(B, N, H, G, d_head);
+  if (part > 0 && ws_bytes >= need + part && aligned16(ws)) {
+    p.S = kl::attn_bwd_splits(B, N, H, G);
+    p.part = reinterpret_cast<float*>(static_cast<char*>(ws) + need);
+  }
   return hip_status(kl::launch_attention_backward(p, static_cast<hipStream_t>(stream)), who);
 }
 

@@ -28,6 +28,7 @@
 // feed the next product as its B operand without a transpose; the transposed
 // A operands come from ds_read_b64_tr_b16 on the row-major tiles.
 
+#include <algorithm>
 #include <type_traits>
 
 #include "attn_tile.h"
@@ -419,8 +420,8 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_dq_kernel(BwdParams p) {
   }
 }
 
-// dV for 192 value rows of one group: every head of the group and every query
-// tile that can see these rows stream through LDS (routed queries and dO, two
+// dV for 192 value rows of one group, or one split's share of its sums: every
+// head of the group and every query tile that can see these rows stream through LDS (routed queries and dO, two
 // stages); the wave's 48 value rows stay in registers as the B operand of
 // S = Q~ V^T and dP = dO V^T, whose results (one value row per lane) are the B
 // operands of dV^T += dO^T P + tau Q~^T dS.
@@ -431,7 +432,7 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_dv_kernel(BwdParams p) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   // Groups fastest in the grid, as in the dQ~ kernel (value tile 0 is the
   // heaviest under the causal mask).
-  const int kvt = blockIdx.y, g = blockIdx.x, b = blockIdx.z;
+  const int kvt = blockIdx.y, g = blockIdx.x, b = blockIdx.z % p.B, split = blockIdx.z / p.B;
   const int R = p.H / p.G;
   const int t = threadIdx.x, lane = t & 63;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
@@ -461,7 +462,9 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_dv_kernel(BwdParams p) {
   const int ntq = (p.N + kTileRows - 1) / kTileRows;
   const int qt0 = p.causal ? (kvt * BKVD) / kTileRows : 0;
   const int per_head = ntq - qt0;
-  const int items = R * per_head;
+  // The pairs of this workgroup: its share of the splits.
+  const int first = (int)((long)R * per_head * split / p.S);
+  const int items = (int)((long)R * per_head * (split + 1) / p.S);
   const TileCopier<D> cp(wave, lane);
   const unsigned char* gQ = reinterpret_cast<const unsigned char*>(p.q);
   const unsigned char* gD = reinterpret_cast<const unsigned char*>(p.dout);
@@ -488,8 +491,8 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_dv_kernel(BwdParams p) {
   const FragOffsets<D> fo(fr, grp);
 
   auto lds_at = [](int a) { return (const lds_u8*)(size_t)(uint32_t)a; };
-  if (items > 0) issue(0);
-  for (int it = 0; it < items; ++it) {
+  if (first < items) issue(first);
+  for (int it = first; it < items; ++it) {
     KL_WAIT_VMCNT(0);
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     __syncthreads();
@@ -625,7 +628,20 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_dv_kernel(BwdParams p) {
     }
   }
 
-  // Lane holds dV^T[16 db + 4 grp + r][kv0 + 16 kb + fr].
+  // Lane holds dV^T[16 db + 4 grp + r][kv0 + 16 kb + fr]; a split leaves its sums
+  // in fp32, laid out as dv.
+  if (p.S > 1) {
+    float* part = p.part + (size_t)split * p.B * p.N * p.G * D;
+#pragma unroll
+    for (int kb = 0; kb < KVB; ++kb) {
+      const int kv = kv0 + kb * 16 + fr;
+      if (kv >= p.N) continue;
+      float* dst = part + (((size_t)b * p.N + kv) * p.G + g) * D + grp * 4;
+#pragma unroll
+      for (int db = 0; db < DB; ++db) *reinterpret_cast<f32x4_t*>(dst + db * 16) = acc[db][kb];
+    }
+    return;
+  }
   uint16_t* __restrict__ out = reinterpret_cast<uint16_t*>(p.dv);
 #pragma unroll
   for (int kb = 0; kb < KVB; ++kb) {
@@ -781,9 +797,11 @@ hipError_t launch_mfma(const BwdParams& p, hipStream_t st) {
     e = set_max_lds(reinterpret_cast<const void*>(bwd_dv_kernel<D>), dv_lds, done);
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL(bwd_dv_kernel<D>, dim3(p.G, (p.N + BKVD - 1) / BKVD, p.B), dim3(kThreads),
+  hipLaunchKernelGGL(bwd_dv_kernel<D>, dim3(p.G, (p.N + BKVD - 1) / BKVD, p.B * p.S), dim3(kThreads),
                      dv_lds, st, p);
-  return hipGetLastError();
+  e = hipGetLastError();
+  if (e != hipSuccess || p.S == 1) return e;
+  return launch_sum_partials_bf16(p.part, p.S, (size_t)p.B * p.N * p.G * D, p.dv, st);
 }
 
 template <typename TO, typename T>
@@ -800,6 +818,21 @@ hipError_t launch_prep(const BwdParams& p, hipStream_t st) {
 }
 
 }  // namespace
+
+// Splits of each dV tile's (head, query tile) pairs over workgroups, each with
+// fp32 partial sums. One workgroup per tile fills the chip only with many tiles;
+// a grouped layer has few, each with every head of its group to walk (12 heads on
+// 2 groups, 2 x 1000 tokens: 24 workgroups, 280 us). Three workgroups per CU even
+// out the causal tiles' lengths; a split of fewer than four pairs costs more in
+// partials than it saves. Forward + backward at a target of 1 / 512 / 768 / 1024
+// workgroups, us: 12 on 2 heads, 8192 tokens 2687 / 997 / 928 / 904, 2000 tokens
+// 664 / 156 / 166 / 168; 32 on 8, 6000 tokens 1655 / 1386 / 1183 / 1158.
+int attn_bwd_splits(int B, int N, int H, int G) {
+  const long tiles = (long)G * B * ((N + BKVD - 1) / BKVD);
+  const long pairs = (long)(H / G) * ((N + kTileRows - 1) / kTileRows);  // of the heaviest tile
+  if (tiles == 0) return 1;
+  return (int)std::max(1L, std::min((768 + tiles - 1) / tiles, pairs / 4));
+}
 
 bool attn_bwd_mfma_supported(const BwdParams& p) {
   return p.dtype == KL_BF16 && (p.D == 64 || p.D == 128) && p.q_stride % 8 == 0 &&

@@ -373,22 +373,25 @@ hipError_t launch_gemm_bf16(const GemmBf16Args& a, hipStream_t st) {
 
 namespace {
 
-// out[i] = bf16(sum over s < S of part[s n + i]), in order of s.
+// out[i] = bf16(sum over s < S of part[s n + i]), in order of s; four elements a
+// thread (n is a multiple of 4: whole heads).
 __global__ __launch_bounds__(256) void sum_partials_kernel(const float* __restrict__ part, int S,
                                                            size_t n, uint16_t* __restrict__ out) {
-  const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
+  const size_t i = ((size_t)blockIdx.x * 256 + threadIdx.x) * 4;
   if (i >= n) return;
-  float acc = 0.f;
-  for (int s = 0; s < S; ++s) acc += part[(size_t)s * n + i];
-  out[i] = __builtin_bit_cast(uint16_t, (__bf16)acc);
+  f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 8
+  for (int s = 0; s < S; ++s) acc += *reinterpret_cast<const f32x4_t*>(part + (size_t)s * n + i);
+#pragma unroll
+  for (int e = 0; e < 4; ++e) out[i + e] = __builtin_bit_cast(uint16_t, (__bf16)acc[e]);
 }
 
 }  // namespace
 
 hipError_t launch_sum_partials_bf16(const float* part, int S, size_t n, void* out, hipStream_t st) {
   if (n == 0) return hipSuccess;
-  if (S <= 0) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(sum_partials_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, part,
+  if (S <= 0 || n % 4 != 0) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(sum_partials_kernel, dim3((unsigned)((n / 4 + 255) / 256)), dim3(256), 0, st, part,
                      S, n, static_cast<uint16_t*>(out));
   return hipGetLastError();
 }

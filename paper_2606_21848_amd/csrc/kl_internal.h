@@ -225,7 +225,10 @@ struct BwdParams {
   float scale;       // tau
   float scale_log2;  // tau * log2(e)
   kl_dtype dtype;
+  int S;             // splits of the dV sums (bf16 MFMA), 1 for none
+  float* part;       // their fp32 partial sums [S, B, N, G, D]
 };
+int attn_bwd_splits(int B, int N, int H, int G);
 bool attn_bwd_mfma_supported(const BwdParams& p);
 hipError_t launch_attention_backward(const BwdParams& p, hipStream_t stream);
 

@@ -77,6 +77,25 @@ def test_attention_backward_matches_oracle(lib, dtype, causal, B, N, H, G, dk, k
     assert_parity(dv, ref_dv, dtype, "dV", FLOOR, scale)
 
 
+@pytest.mark.parametrize("B,N,H,G,dk", [(1, 255, 4, 1, 64), (2, 193, 6, 2, 128), (1, 700, 3, 3, 128)])
+def test_attention_backward_split_sums(lib, B, N, H, G, dk):
+    """dV from the fp32 partial sums of several workgroups, and from one workgroup
+    per tile when the workspace holds only the row sums: both at the oracle's."""
+    say(f"split dV sums B={B} N={N} H={H} G={G} dk={dk}")
+    Qr, V, dO = _qvd(B, N, H, G, dk, 75, torch.bfloat16)
+    q, v, g = Qr.to(DEV), V.to(DEV), dO.to(DEV)
+    rows = -(-B * N * H * 4 // 256) * 256
+    assert kb.attention_backward_workspace_bytes(B, N, H) > rows
+    for causal in (True, False):
+        out, lse = kb.keyless_attention_forward(q, v, causal=causal)
+        _, ref_dv = K.keyless_attention_backward(to64(Qr), to64(V), to64(dO), H, G, dk,
+                                                 causal=causal)
+        for ws in (None, torch.empty(rows, dtype=torch.uint8, device=DEV)):
+            _, dv = kb.keyless_attention_backward(q, v, out, g, lse, causal=causal, workspace=ws)
+            torch.cuda.synchronize()
+            assert_parity(dv, ref_dv, torch.bfloat16, "dV", FLOOR)
+
+
 def test_attention_backward_is_deterministic(lib):
     B, N, H, G, dk = 1, 700, 8, 2, 128
     say("attention backward determinism")
