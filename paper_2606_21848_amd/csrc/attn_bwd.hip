@@ -420,6 +420,164 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_dq_kernel(BwdParams p) {
   }
 }
 
+// dQ~ for few query tiles, from the forward's fp32 output: 32 query rows of one
+// head per workgroup, its four waves sharing the value tiles (32 rows, tile t to
+// wave t % 4), each through a private two-stage ring with no barrier; their sums
+// are added once at the end, in wave order. Otherwise as bwd_dq_kernel.
+template <int D>
+__global__ __launch_bounds__(kThreads, 2) void bwd_dq_split_kernel(BwdParams p) {
+  constexpr int QB = 2, NW = 4, RV = 32, BQ = 16 * QB;
+  using TL = AttnTile<D, RV>;
+  using Copier = WaveCopier<D, RV>;
+  constexpr int KS = D / 32, DB = D / 16, RING = 2 * TL::BYTES;
+  static_assert(RING == BQ * D * 4, "a wave's results fit its ring");
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+  const int ntq = (p.N + BQ - 1) / BQ;
+  const int qt = p.causal ? (ntq - 1 - (int)blockIdx.y) : (int)blockIdx.y;
+  const int h = blockIdx.x, b = blockIdx.z;
+  const int g = h / (p.H / p.G);
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int fr = lane & 15, grp = lane >> 4;
+  const int q0 = qt * BQ;
+
+  const unsigned char* gV =
+      reinterpret_cast<const unsigned char*>(p.v) + ((size_t)b * p.N * p.v_stride + (size_t)g * D) * 2;
+  const size_t vrow = (size_t)p.v_stride * 2;
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_u8*)smem;
+  const uint32_t ring = lds0 + wave * RING;
+  const Copier cp(lane);
+  const int last_row = p.causal ? min(q0 + BQ, p.N) : p.N;
+  const int ntiles = (last_row + RV - 1) / RV;
+  if (wave < ntiles) cp.issue(gV, vrow, wave * RV, p.N, lane, ring);
+
+  const uint16_t* __restrict__ Q = reinterpret_cast<const uint16_t*>(p.q);
+  const uint16_t* __restrict__ dO = reinterpret_cast<const uint16_t*>(p.dout);
+  const float c = p.scale_log2;
+  bf16x8_t qf[QB][KS], df[QB][KS];
+  f32x4_t nlse[QB], ndd[QB], acc[DB][QB];
+#pragma unroll
+  for (int qb = 0; qb < QB; ++qb) {
+    const int qq = min(q0 + qb * 16 + fr, p.N - 1);
+    const uint16_t* sq = Q + ((size_t)b * p.N + qq) * p.q_stride + (size_t)h * D + grp * 8;
+    const uint16_t* sd = dO + ((size_t)b * p.N + qq) * p.o_stride + (size_t)h * D + grp * 8;
+    const float* o = p.out_f32 + (((size_t)b * p.N + qq) * p.H + h) * D + grp * 8;
+    float d0 = 0.f;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      const u32x4 raw = *reinterpret_cast<const u32x4*>(sq + ks * 32);
+      const u32x4 gr = *reinterpret_cast<const u32x4*>(sd + ks * 32);
+      const f32x4_t o0 = *reinterpret_cast<const f32x4_t*>(o + ks * 32);
+      const f32x4_t o1 = *reinterpret_cast<const f32x4_t*>(o + ks * 32 + 4);
+      u32x4 w;
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        w[j] = pack2(__uint_as_float(raw[j] << 16) * c, __uint_as_float(raw[j] & 0xFFFF0000u) * c);
+      qf[qb][ks] = __builtin_bit_cast(bf16x8_t, w);
+      df[qb][ks] = __builtin_bit_cast(bf16x8_t, gr);
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        d0 = fmaf(__uint_as_float(gr[j] << 16), o0[2 * j], d0);
+        d0 = fmaf(__uint_as_float(gr[j] & 0xFFFF0000u), o0[2 * j + 1], d0);
+        d0 = fmaf(__uint_as_float(gr[j + 2] << 16), o1[2 * j], d0);
+        d0 = fmaf(__uint_as_float(gr[j + 2] & 0xFFFF0000u), o1[2 * j + 1], d0);
+      }
+    }
+    d0 += __shfl_xor(d0, 16);
+    d0 += __shfl_xor(d0, 32);
+    const size_t row = ((size_t)b * p.H + h) * p.N + qq;
+    if (wave == 0 && grp == 0 && q0 + qb * 16 + fr < p.N) p.Dd[row] = d0;
+    const float l2 = p.lse[row] * kLog2e;
+    nlse[qb] = f32x4_t{-l2, -l2, -l2, -l2};
+    ndd[qb] = f32x4_t{-d0, -d0, -d0, -d0};
+#pragma unroll
+    for (int i = 0; i < DB; ++i) acc[i][qb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  }
+  const FragOffsets<D> fo(fr, grp);
+  int stage = 0;
+  for (int jt = wave; jt < ntiles; jt += NW) {
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the other stage has been read
+    if (jt + NW < ntiles) {
+      cp.issue(gV, vrow, (jt + NW) * RV, p.N, lane, ring + (stage ^ 1) * TL::BYTES);
+      KL_WAIT_VMCNT(Copier::COPIES);
+    } else {
+      KL_WAIT_VMCNT(0);
+    }
+    asm volatile("" ::: "memory");
+    const int j0 = jt * RV;
+    const FragOffsets<D> fi = fo.at(ring + stage * TL::BYTES);
+    auto at = [](int a) { return (const lds_u8*)(uintptr_t)(uint32_t)a; };
+    f32x4_t sc[2][QB], dp[2][QB];
+    bf16x8_t va[2][KS];
+#pragma unroll
+    for (int hh = 0; hh < 2; ++hh)
+#pragma unroll
+      for (int kd = 0; kd < KS; ++kd)
+        va[hh][kd] = *reinterpret_cast<const __attribute__((address_space(3))) bf16x8_t*>(
+            at(fi.s(kd) + hh * 16 * TL::ROW));
+#pragma unroll
+    for (int hh = 0; hh < 2; ++hh)
+#pragma unroll
+      for (int kd = 0; kd < KS; ++kd)
+#pragma unroll
+        for (int qb = 0; qb < QB; ++qb) {
+          sc[hh][qb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+              va[hh][kd], qf[qb][kd], kd == 0 ? nlse[qb] : sc[hh][qb], 0, 0, 0);
+          dp[hh][qb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+              va[hh][kd], df[qb][kd], kd == 0 ? ndd[qb] : dp[hh][qb], 0, 0, 0);
+        }
+    const bool edge = (p.causal && j0 + RV - 1 > q0) || (j0 + RV > p.N);
+    bf16x8_t pf[QB];
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) {
+      float ds[2][4];
+#pragma unroll
+      for (int hh = 0; hh < 2; ++hh)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) ds[hh][r] = fast_exp2(sc[hh][qb][r]) * dp[hh][qb][r];
+      if (edge) {  // uniform
+#pragma unroll
+        for (int hh = 0; hh < 2; ++hh)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const int kv = j0 + hh * 16 + grp * 4 + r;
+            ds[hh][r] = (kv >= p.N || (p.causal && kv > q0 + qb * 16 + fr)) ? 0.f : ds[hh][r];
+          }
+      }
+      pf[qb] = __builtin_bit_cast(bf16x8_t, u32x4{pack2(ds[0][0], ds[0][1]), pack2(ds[0][2], ds[0][3]),
+                                                  pack2(ds[1][0], ds[1][1]), pack2(ds[1][2], ds[1][3])});
+    }
+#pragma unroll
+    for (int db = 0; db < DB; ++db) {
+      const lds_u8* src = at(fi.t(db));
+      const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+          (__attribute__((address_space(3))) s16x4*)(src));
+      const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+          (__attribute__((address_space(3))) s16x4*)(src + 16 * TL::ROW));
+      const bf16x8_t a = __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+#pragma unroll
+      for (int qb = 0; qb < QB; ++qb)
+        acc[db][qb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, pf[qb], acc[db][qb], 0, 0, 0);
+    }
+    stage ^= 1;
+  }
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+  for (int qb = 0; qb < QB; ++qb)
+#pragma unroll
+    for (int db = 0; db < DB; ++db)
+      WaveSums<D>::put(ring, qb * 16 + fr, 4 * db + grp, acc[db][qb] * p.scale);
+  __syncthreads();
+  uint16_t* __restrict__ out = reinterpret_cast<uint16_t*>(p.dq);
+  for (int e = threadIdx.x; e < BQ * D / 4; e += kThreads) {
+    const int row = e / (D / 4), piece = e % (D / 4);
+    if (q0 + row >= p.N) continue;
+    const f32x4_t x = WaveSums<D>::template get<NW>(lds0, RING, row, piece);
+    *reinterpret_cast<u32x2*>(out + ((size_t)b * p.N + q0 + row) * p.dq_stride + (size_t)h * D +
+                              piece * 4) = u32x2{pack2(x[0], x[1]), pack2(x[2], x[3])};
+  }
+}
+
 // dV for 192 value rows of one group, or one split's share of its sums: every
 // head of the group and every query tile that can see these rows stream through LDS (routed queries and dO, two
 // stages); the wave's 48 value rows stay in registers as the B operand of
@@ -783,7 +941,15 @@ hipError_t launch_simple(const BwdParams& p, hipStream_t st) {
 template <int D>
 hipError_t launch_mfma(const BwdParams& p, hipStream_t st) {
   using TL = AttnTile<D, kTileRows>;
-  if (p.out_f32)
+  // Fewer 128-row workgroups than about one per CU: the split form. Forward +
+  // backward, us (this form / the other): 12 heads, 1000 tokens (96 workgroups)
+  // 62.8 / 75.6, 3000 (288) 213 / 231; 32 heads, 1000 (256) 111 / 112, 1500 (384)
+  // 172 / 169.
+  constexpr int split_lds = 4 * 2 * AttnTile<D, 32>::BYTES;
+  if (p.out_f32 && (long)p.H * p.B * ((p.N + BQD - 1) / BQD) < 300)
+    hipLaunchKernelGGL(bwd_dq_split_kernel<D>, dim3(p.H, (p.N + 31) / 32, p.B), dim3(kThreads),
+                       split_lds, st, p);
+  else if (p.out_f32)
     hipLaunchKernelGGL((bwd_dq_kernel<D, false>), dim3(p.H, (p.N + BQD - 1) / BQD, p.B),
                        dim3(kThreads), NSTAGE * TL::BYTES, st, p);
   else

@@ -9,6 +9,8 @@
 #include <hip/hip_runtime.h>
 #include <cstdint>
 
+#include "kl_device.h"
+
 namespace kl {
 
 template <int D, int ROWS>
@@ -64,6 +66,57 @@ struct FragOffsets {
     f.sbase += (int)base;
     f.tbase += (int)base;
     return f;
+  }
+};
+
+// One wave's direct-to-LDS copy of ROWS rows (row0 .., clamped to n_rows - 1) of
+// a row-major bf16 matrix, columns [0, D) from `g`, into an AttnTile<D, ROWS>:
+// instruction c fills rows c RPC .. + RPC - 1, lane L the physical chunk
+// L % CHUNKS of its row, with the logical chunk that the swizzle puts there.
+template <int D, int ROWS>
+struct WaveCopier {
+  using T = AttnTile<D, ROWS>;
+  static constexpr int COPIES = T::BYTES / 1024, RPC = 1024 / T::ROW;
+  uint32_t chunk[COPIES];
+  __device__ __forceinline__ explicit WaveCopier(int lane) {
+#pragma unroll
+    for (int c = 0; c < COPIES; ++c) {
+      const int r = c * RPC + lane / T::CHUNKS, pc = lane % T::CHUNKS;
+      chunk[c] = (uint32_t)(T::swz(r, pc) * 16);  // an XOR: its own inverse
+    }
+  }
+  __device__ __forceinline__ void issue(const unsigned char* g, size_t row_bytes, int row0, int n_rows,
+                                        int lane, uint32_t lds) const {
+#pragma unroll
+    for (int c = 0; c < COPIES; ++c) {
+      const int r0 = row0 + c * RPC;  // uniform
+      const int r0c = min(r0, n_rows - 1);
+      const int rl = min(r0 + lane / T::CHUNKS, n_rows - 1) - r0c;
+      copy_to_lds(g + (size_t)r0c * row_bytes, (uint32_t)(rl * row_bytes) + chunk[c], lds + c * 1024);
+    }
+  }
+};
+
+// Sums over NW waves of their [ROWS][D] fp32 results (each wave's in its own
+// place of LDS, `stride` bytes apart): put() stores a wave's row piece, get() adds
+// the waves' pieces in wave order. A row's 16-byte pieces are XOR-swizzled by the
+// row so that 16 rows of one piece hit distinct banks.
+template <int D>
+struct WaveSums {
+  typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4_t;
+  typedef __attribute__((address_space(3))) f32x4_t lds_f32x4;
+  static __device__ __forceinline__ uint32_t at(int row, int piece) {
+    return (uint32_t)(row * D * 4 + ((piece ^ (row & 15)) << 4));
+  }
+  static __device__ __forceinline__ void put(uint32_t base, int row, int piece, f32x4_t x) {
+    *(lds_f32x4*)(base + at(row, piece)) = x;
+  }
+  template <int NW>
+  static __device__ __forceinline__ f32x4_t get(uint32_t base, uint32_t stride, int row, int piece) {
+    f32x4_t x = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int w = 0; w < NW; ++w) x += *(lds_f32x4*)(base + w * stride + at(row, piece));
+    return x;
   }
 };
 

@@ -396,6 +396,216 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bf16_kernel(AttnParams p) {
   }
 }
 
+// The same attention for few query tiles (short prompts, few heads): a workgroup
+// owns 32 query rows of one head and its four waves share the value tiles (32
+// rows, tile t to wave t % 4), each through a private two-stage ring with no
+// barrier, and meet only to merge (m, l, O). The longest chain of tiles is a
+// quarter of a query's, and there are six times the workgroups of the 192-row
+// form; what that costs is LDS reads (two products per fragment instead of three).
+template <int D>
+__global__ __launch_bounds__(kThreads, 2) void attn_bf16_split_kernel(AttnParams p) {
+  constexpr int QB = 2, NW = 4, RV = 32, BQ = 16 * QB;
+  using T = AttnTile<D, RV>;
+  using Copier = WaveCopier<D, RV>;
+  constexpr int KS = D / 32, DB = D / 16, RING = 2 * T::BYTES;
+  static_assert(RING == BQ * D * 4, "a wave's results fit its ring");
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+  __shared__ float s_ml[NW][BQ][2];
+  const int ntq = (p.N + BQ - 1) / BQ;
+  const int qt = p.causal ? (ntq - 1 - (int)blockIdx.y) : (int)blockIdx.y;
+  const int h = blockIdx.x, b = blockIdx.z;
+  const int g = h / (p.H / p.G);
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int fr = lane & 15, grp = lane >> 4;
+  const int q0 = qt * BQ;
+
+  const unsigned char* gV =
+      reinterpret_cast<const unsigned char*>(p.v) + ((size_t)b * p.Nk * p.v_stride + (size_t)g * D) * 2;
+  const size_t row_bytes = (size_t)p.v_stride * 2;
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_u8*)smem;
+  const uint32_t ring = lds0 + wave * RING;
+  const Copier cp(lane);
+  const int last_row = p.causal ? min(q0 + BQ, p.Nk) : p.Nk;
+  const int ntiles = (last_row + RV - 1) / RV;
+  if (wave < ntiles) cp.issue(gV, row_bytes, wave * RV, p.Nk, lane, ring);
+
+  const uint16_t* __restrict__ Q = reinterpret_cast<const uint16_t*>(p.q);
+  const float c = p.scale_log2;
+  bf16x8_t qf[QB][KS];
+#pragma unroll
+  for (int qb = 0; qb < QB; ++qb) {
+    const int qq = min(q0 + qb * 16 + fr, p.N - 1);
+    const uint16_t* src = Q + ((size_t)b * p.N + qq) * p.q_stride + (size_t)h * D + grp * 8;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      const u32x4 raw = *reinterpret_cast<const u32x4*>(src + ks * 32);
+      u32x4 w;
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        w[j] = pack2(__uint_as_float(raw[j] << 16) * c, __uint_as_float(raw[j] & 0xFFFF0000u) * c);
+      qf[qb][ks] = __builtin_bit_cast(bf16x8_t, w);
+    }
+  }
+  f32x4_t o[DB][QB], osum[QB];
+  float m[QB];
+#pragma unroll
+  for (int qb = 0; qb < QB; ++qb) {
+#pragma unroll
+    for (int i = 0; i < DB; ++i) o[i][qb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    osum[qb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    m[qb] = 0.f;
+  }
+  const bf16x8_t ones = __builtin_bit_cast(
+      bf16x8_t, u32x4{0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u});
+  const FragOffsets<D> fo(fr, grp);
+  int stage = 0;
+  for (int jt = wave; jt < ntiles; jt += NW) {
+    // This wave's reads of the other stage have returned; refill it, then wait for
+    // this tile's copies.
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    if (jt + NW < ntiles) {
+      cp.issue(gV, row_bytes, (jt + NW) * RV, p.Nk, lane, ring + (stage ^ 1) * T::BYTES);
+      KL_WAIT_VMCNT(Copier::COPIES);
+    } else {
+      KL_WAIT_VMCNT(0);
+    }
+    asm volatile("" ::: "memory");
+    const int j0 = jt * RV;
+    const FragOffsets<D> fi = fo.at(ring + stage * T::BYTES);
+    auto at = [](int a) { return (const lds_u8*)(uintptr_t)(uint32_t)a; };
+    f32x4_t sc[2][QB];
+    bf16x8_t sa[2][KS];
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks)
+        sa[kb][ks] = *reinterpret_cast<const __attribute__((address_space(3))) bf16x8_t*>(
+            at(fi.s(ks) + kb * 16 * T::ROW));
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+        for (int qb = 0; qb < QB; ++qb)
+          sc[kb][qb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+              sa[kb][ks], qf[qb][ks], ks == 0 ? f32x4_t{-m[qb], -m[qb], -m[qb], -m[qb]} : sc[kb][qb],
+              0, 0, 0);
+    if ((p.causal && j0 + RV - 1 > q0) || (j0 + RV > p.Nk)) {
+#pragma unroll
+      for (int qb = 0; qb < QB; ++qb) {
+        const int q = q0 + qb * 16 + fr;
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const int kv = j0 + kb * 16 + grp * 4 + r;
+            if (kv >= p.Nk || (p.causal && kv > q)) sc[kb][qb][r] = -INFINITY;
+          }
+      }
+    }
+    const bool first = jt == wave;
+    float lm[QB];
+    bool grow = first;
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) {
+      lm[qb] = max3(max3(sc[0][qb][0], sc[0][qb][1], sc[0][qb][2]),
+                    max3(sc[0][qb][3], sc[1][qb][0], sc[1][qb][1]), fmaxf(sc[1][qb][2], sc[1][qb][3]));
+      grow |= lm[qb] > 8.f;
+    }
+    if (__builtin_amdgcn_ballot_w64(grow)) {
+#pragma unroll
+      for (int qb = 0; qb < QB; ++qb) {
+        float t = fmaxf(lm[qb], __shfl_xor(lm[qb], 16));
+        t = fmaxf(t, __shfl_xor(t, 32));
+        // The wave's first tile sets the reference, except for a query that sees
+        // none of its rows (nor, under the causal mask, any of a later tile's).
+        const float d = first ? (t == -INFINITY ? 0.f : t) : (t > 8.f ? t : 0.f);
+        m[qb] += d;
+        const float alpha = fast_exp2(first ? 0.f : -d);
+#pragma unroll
+        for (int i = 0; i < DB; ++i) o[i][qb] *= alpha;
+        osum[qb] *= alpha;
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb) sc[kb][qb] -= d;
+      }
+    }
+    bf16x8_t pf[QB];
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) {
+      u32x4 w;
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb) {
+        f32x4_t x = sc[kb][qb];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) x[r] = fast_exp2(x[r]);
+        w[2 * kb] = pack2(x[0], x[1]);
+        w[2 * kb + 1] = pack2(x[2], x[3]);
+      }
+      pf[qb] = __builtin_bit_cast(bf16x8_t, w);
+    }
+    bf16x8_t av[DB];
+#pragma unroll
+    for (int db = 0; db < DB; ++db) {
+      const lds_u8* src = at(fi.t(db));
+      const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+          (__attribute__((address_space(3))) s16x4*)(src));
+      const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+          (__attribute__((address_space(3))) s16x4*)(src + 16 * T::ROW));
+      av[db] = __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+    }
+#pragma unroll
+    for (int db = 0; db < DB; ++db)
+#pragma unroll
+      for (int qb = 0; qb < QB; ++qb)
+        o[db][qb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[db], pf[qb], o[db][qb], 0, 0, 0);
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb)
+      osum[qb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, pf[qb], osum[qb], 0, 0, 0);
+    stage ^= 1;
+  }
+
+  // Merge: each wave's (m, l) of its queries, then the waves' outputs scaled to
+  // the common reference, added in wave order.
+  if (grp == 0) {
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) {
+      s_ml[wave][qb * 16 + fr][0] = osum[qb][0] > 0.f ? m[qb] : -INFINITY;
+      s_ml[wave][qb * 16 + fr][1] = osum[qb][0];
+    }
+  }
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  __syncthreads();
+#pragma unroll
+  for (int qb = 0; qb < QB; ++qb) {
+    const int row = qb * 16 + fr;
+    float mm = s_ml[0][row][0], l = 0.f;
+#pragma unroll
+    for (int w = 1; w < NW; ++w) mm = fmaxf(mm, s_ml[w][row][0]);
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      const float mw = s_ml[w][row][0];
+      l += mw == -INFINITY ? 0.f : s_ml[w][row][1] * fast_exp2(mw - mm);
+    }
+    if (p.lse && wave == 0 && grp == 0 && q0 + row < p.N)
+      p.lse[((size_t)b * p.H + h) * p.N + q0 + row] = (mm + __log2f(l)) * 0.69314718055994531f;
+    const float f = osum[qb][0] > 0.f ? fast_exp2(m[qb] - mm) / l : 0.f;
+#pragma unroll
+    for (int db = 0; db < DB; ++db) WaveSums<D>::put(ring, row, 4 * db + grp, o[db][qb] * f);
+  }
+  __syncthreads();
+  uint16_t* __restrict__ O = reinterpret_cast<uint16_t*>(p.out);
+  for (int e = threadIdx.x; e < BQ * D / 4; e += kThreads) {
+    const int row = e / (D / 4), piece = e % (D / 4);
+    if (q0 + row >= p.N) continue;
+    const f32x4_t x = WaveSums<D>::template get<NW>(lds0, RING, row, piece);
+    const size_t bq = (size_t)b * p.N + q0 + row;
+    if (p.out_f32) *reinterpret_cast<f32x4_t*>(p.out_f32 + (bq * p.H + h) * D + piece * 4) = x;
+    *reinterpret_cast<u32x2*>(O + bq * p.o_stride + (size_t)h * D + piece * 4) =
+        u32x2{pack2(x[0], x[1]), pack2(x[2], x[3])};
+  }
+}
+
 template <int D, int QB>
 hipError_t launch_attn_qb(const AttnParams& p, hipStream_t st) {
   constexpr int BQ = 4 * 16 * QB;
@@ -406,6 +616,18 @@ hipError_t launch_attn_qb(const AttnParams& p, hipStream_t st) {
 
 template <int D>
 hipError_t launch_attn(const AttnParams& p, hipStream_t st) {
+  // Fewer 192-row (128-row) workgroups than about one per CU: the split form. At
+  // 12 heads, causal, whole prefill in us (this form / the other): 517 tokens (36
+  // workgroups) 19.4 / 29.2, 2000 (132) 43.5 / 64.0, 4000 (252) 100 / 116, 8000
+  // (504) 287 / 238; 32 heads, 1000 (192) 84.6 / 90.2, 2000 (352) 161 / 156; 32
+  // heads, 500 queries on 4000 values (128) 177 / 197.
+  const int bq = p.causal ? 192 : 128;
+  if ((long)p.H * p.B * ((p.N + bq - 1) / bq) < 300) {
+    constexpr int lds = 4 * 2 * AttnTile<D, 32>::BYTES;
+    hipLaunchKernelGGL(attn_bf16_split_kernel<D>, dim3(p.H, (p.N + 31) / 32, p.B), dim3(kThreads), lds,
+                       st, p);
+    return hipGetLastError();
+  }
   return p.causal ? launch_attn_qb<D, 3>(p, st) : launch_attn_qb<D, 2>(p, st);
 }
 

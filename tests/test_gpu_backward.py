@@ -77,6 +77,35 @@ def test_attention_backward_matches_oracle(lib, dtype, causal, B, N, H, G, dk, k
     assert_parity(dv, ref_dv, dtype, "dV", FLOOR, scale)
 
 
+@pytest.mark.parametrize("keep_f32", [False, True])
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("B,N,H,G,dk", [(40, 77, 8, 2, 64), (60, 200, 4, 4, 128), (300, 1, 4, 1, 128)])
+def test_attention_of_many_sequences(lib, causal, B, N, H, G, dk, keep_f32):
+    """Enough query tiles to fill the chip, so that the forms with whole workgroups
+    per query tile run, on short ragged sequences."""
+    say(f"attention of many sequences B={B} N={N} H={H} G={G} dk={dk} causal={causal} {keep_f32}")
+    Qr, V, dO = _qvd(B, N, H, G, dk, 76, torch.bfloat16)
+    q, v, g = Qr.to(DEV), V.to(DEV), dO.to(DEV)
+    o32 = torch.empty((B, N, H, dk), dtype=torch.float32, device=DEV) if keep_f32 else None
+    out, lse = kb.keyless_attention_forward(q, v, causal=causal, out_f32=o32)
+    dq, dv = kb.keyless_attention_backward(q, v, out, g, lse, causal=causal, out_f32=o32)
+    torch.cuda.synchronize()
+    # A score is off by at most 2^-9 tau sum |q v| (q~ rounded to bf16 once more),
+    # 0.014 for 128 products of N(0, 1) pairs.
+    ref_lse = K.attention_logsumexp(to64(Qr), to64(V), H, G, dk, causal=causal)
+    assert np.abs(to64(lse) - ref_lse).max() <= 2e-2
+    refs = K.keyless_attention_backward(to64(Qr), to64(V), to64(dO), H, G, dk, causal=causal)
+    # Over tens of thousands of rows some dQ~ cancel to a small part of their terms,
+    # whose bf16 rounding then shows in that row. So here by the 2-norm of the
+    # tensor: q~, P, dS and the result are each rounded by at most 2^-9 of
+    # themselves, 4 x 2^-9 = 7.8e-3 in all (a row of one value has dQ~ = 0).
+    for got, ref, what in zip((dq, dv), refs, ("dQ~", "dV")):
+        off = np.linalg.norm(to64(got) - ref)
+        assert off <= 7.8e-3 * np.linalg.norm(refs[1] if N == 1 else ref), what
+    if keep_f32:
+        assert torch.equal(o32.to(torch.bfloat16), out)
+
+
 @pytest.mark.parametrize("B,N,H,G,dk", [(1, 255, 4, 1, 64), (2, 193, 6, 2, 128), (1, 700, 3, 3, 128)])
 def test_attention_backward_split_sums(lib, B, N, H, G, dk):
     """dV from the fp32 partial sums of several workgroups, and from one workgroup
