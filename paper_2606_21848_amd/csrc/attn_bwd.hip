@@ -446,7 +446,7 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_dq_split_kernel(BwdParams p) 
   const size_t vrow = (size_t)p.v_stride * 2;
   const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_u8*)smem;
   const uint32_t ring = lds0 + wave * RING;
-  const Copier cp(lane);
+  const Copier cp(lane, vrow);
   const int last_row = p.causal ? min(q0 + BQ, p.N) : p.N;
   const int ntiles = (last_row + RV - 1) / RV;
   if (wave < ntiles) cp.issue(gV, vrow, wave * RV, p.N, lane, ring);

@@ -77,8 +77,10 @@ template <int D, int ROWS>
 struct WaveCopier {
   using T = AttnTile<D, ROWS>;
   static constexpr int COPIES = T::BYTES / 1024, RPC = 1024 / T::ROW;
-  uint32_t chunk[COPIES];
-  __device__ __forceinline__ explicit WaveCopier(int lane) {
+  uint32_t chunk[COPIES];  // byte offset of the fetched chunk in its row
+  uint32_t lane_row;       // and of the lane's row in its instruction's rows
+  __device__ __forceinline__ WaveCopier(int lane, size_t row_bytes)
+      : lane_row((uint32_t)(lane / T::CHUNKS) * (uint32_t)row_bytes) {
 #pragma unroll
     for (int c = 0; c < COPIES; ++c) {
       const int r = c * RPC + lane / T::CHUNKS, pc = lane % T::CHUNKS;
@@ -87,12 +89,19 @@ struct WaveCopier {
   }
   __device__ __forceinline__ void issue(const unsigned char* g, size_t row_bytes, int row0, int n_rows,
                                         int lane, uint32_t lds) const {
+    if (row0 + ROWS <= n_rows) {  // uniform: whole tile
+      const unsigned char* base = g + (size_t)row0 * row_bytes;
 #pragma unroll
-    for (int c = 0; c < COPIES; ++c) {
-      const int r0 = row0 + c * RPC;  // uniform
-      const int r0c = min(r0, n_rows - 1);
-      const int rl = min(r0 + lane / T::CHUNKS, n_rows - 1) - r0c;
-      copy_to_lds(g + (size_t)r0c * row_bytes, (uint32_t)(rl * row_bytes) + chunk[c], lds + c * 1024);
+      for (int c = 0; c < COPIES; ++c)
+        copy_to_lds(base + (size_t)(c * RPC) * row_bytes, lane_row + chunk[c], lds + c * 1024);
+    } else {
+#pragma unroll
+      for (int c = 0; c < COPIES; ++c) {
+        const int r0 = row0 + c * RPC;
+        const int r0c = min(r0, n_rows - 1);
+        const int rl = min(r0 + lane / T::CHUNKS, n_rows - 1) - r0c;
+        copy_to_lds(g + (size_t)r0c * row_bytes, (uint32_t)(rl * row_bytes) + chunk[c], lds + c * 1024);
+      }
     }
   }
 };
