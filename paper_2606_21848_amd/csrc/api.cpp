@@ -88,6 +88,7 @@ int cache_capacity(const kl_value_cache* c) {
 
 // Work split of a decode call.
 //  - chunk_rows > 0: split mode with that many rows per split (grid S x G x B).
+//  - Little cache per pair: see one_wide_split.
 //  - A contiguous cache with at least one (b, g) pair per compute unit: one
 //    workgroup per pair streams its whole cache and writes the output directly.
 //  - At most kSmallBatch sequences: split mode with splits sized from the
@@ -134,6 +135,24 @@ DecodePlan plan_decode(const kl_value_cache* c, int B, int chunk_rows) {
   }
   pl.S = cap > 0 ? (cap + pl.chunk - 1) / pl.chunk : 1;
   return pl;
+}
+
+// Whether one wide workgroup (8 or 16 waves) per (b, g) pair decodes the whole
+// capacity, without splits or a merge kernel. One CU streams about 64 KB a
+// microsecond, and the merge launch costs about 4 us: against the fixed splits of
+// at most kSmallBatch sequences the line is at 256 KiB per pair (12 heads on 2
+// groups, 1000 rows: 8.9 / 13.6 us, 2000 rows: 12.7 / 10.1), against the balanced
+// mode at 512 KiB (64 pairs: 15.2 / 18.5 us), and at 1 MiB with half the CUs busy
+// (224 pairs: 37.2 / 44.7; 64 pairs: 24.9 / 21.3). On the vector ALU each head of a
+// group adds its own arithmetic per row (fp32, 4 heads per group, 12 x 2000 rows
+// of 64: 22.4 / 17.9), so there a group counts with its heads.
+bool one_wide_split(const kl_value_cache* c, int B, int R) {
+  const long pairs = (long)B * c->G;
+  const bool valu = !(c->dtype == KL_BF16 && c->d_head == 128);
+  const long bytes = (long)cache_capacity(c) * c->d_head * (long)elem_bytes(c->dtype) * (valu ? R : 1);
+  if (bytes <= 0 || pairs >= kComputeUnits) return false;
+  const long most = B <= kSmallBatch ? 256L << 10 : (pairs >= kComputeUnits / 2 ? 1024L << 10 : 512L << 10);
+  return bytes <= most;
 }
 
 // Workspace: split partials (acc[d], m, l) per (b, h, split), none with a
@@ -184,7 +203,9 @@ int decode_common(const void* q, const kl_value_cache* k_cache, const kl_value_c
   if (chunk_rows < 0 || chunk_rows % 64 != 0)
     return fail(KL_ERR_INVALID_ARG, "%s: chunk_rows=%d must be a multiple of 64", who, chunk_rows);
   if (B == 0) return KL_OK;
-  const DecodePlan pl = plan_decode(v_cache, B, chunk_rows);
+  DecodePlan pl = plan_decode(v_cache, B, chunk_rows);
+  const bool wide = !k_cache && chunk_rows == 0 && one_wide_split(v_cache, B, R);
+  if (wide) pl = DecodePlan{(cache_capacity(v_cache) + 63) / 64 * 64, 1, false};
   if (pl.S > kl::kMaxSplits)
     return fail(KL_ERR_UNSUPPORTED, "%s: %d splits exceed the maximum of %d (use larger chunks)",
                 who, pl.S, kl::kMaxSplits);
@@ -202,8 +223,20 @@ int decode_common(const void* q, const kl_value_cache* k_cache, const kl_value_c
   p.lengths = lengths;
   p.vnew = vnew;
   p.out = out;
+  // Fixed splits that leave each CU at most one workgroup take wide ones too: half
+  // or a quarter of the tiles per wave (batch 1, 12 heads on 2 groups, 2048 rows: 9.8
+  // -> 8.9 us; with two workgroups per CU, 512 splits, 11.7 -> 13.5).
+  p.wide = wide || (!k_cache && chunk_rows == 0 && !pl.balanced && pl.S > 1 &&
+                    (long)B * G * pl.S <= kComputeUnits);
   p.balanced = pl.balanced;
   p.nwg = kBalancedWorkgroups;
+  if (pl.balanced && R == 32 && !k_cache) {
+    // 32 heads merge 16 KiB per wave: one workgroup of 8 waves per CU instead of
+    // two of 4 halves the partials (latent decode, batch 32 x 16384 rows: 46.4 ->
+    // 41.2 us; 16 heads on 4 waves stay faster, 30.8 against 32.0).
+    p.wide = true;
+    p.nwg = kComputeUnits;
+  }
   if (pl.balanced) {
     p.plan = static_cast<int*>(ws);
     p.part = reinterpret_cast<float*>(static_cast<char*>(ws) + plan_bytes(B));

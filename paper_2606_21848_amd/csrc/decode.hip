@@ -1,6 +1,6 @@
 // Value-only-cache decode (Section 3) and the standard K+V comparison decode.
 //
-// Split-K over the cache length. A workgroup (4 waves) owns one
+// Split-K over the cache length. A workgroup (4 waves, or 8 or 16) owns one
 // (sequence b, value group g, split s) and the R = H/G query heads of that
 // group. Each wave walks 16-row tiles of the split; a lane group of LPR lanes
 // holds one cache row per 16-byte load, so one wave-wide load moves RPL whole
@@ -11,7 +11,9 @@
 //
 // With one split per sequence (enough (b, g) pairs to fill the chip) the
 // workgroup walks the whole cache of its pair and writes the output directly
-// (four waves: eight ran 3% slower on the batch-8 step). Otherwise each split
+// (four waves: eight ran 3% slower on the batch-8 step). Where the launch leaves
+// each CU at most one workgroup, it has 8 or 16 waves (wide_waves), and little
+// cache per pair is one such workgroup without splits. Otherwise each split
 // emits (acc[D], m, l) in fp32 to the workspace and decode_combine merges the
 // splits of each (b, h) in split order.
 
@@ -80,9 +82,9 @@ typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 
 // Stages of the per-wave LDS ring: as many as fit in 64 KiB per 4-wave
-// workgroup (two per CU) or 96 KiB per 8-wave one, at least 2 and at most 4.
+// workgroup (two per CU) or 128 KiB per larger one, at least 2 and at most 4.
 constexpr int stage_count(int stage_bytes, int waves) {
-  const int n = (waves >= 8 ? 98304 : 65536) / (stage_bytes * waves);
+  const int n = (waves >= 8 ? 131072 : 65536) / (stage_bytes * waves);
   return n < 2 ? 2 : (n > 4 ? 4 : n);
 }
 
@@ -896,6 +898,38 @@ __global__ __launch_bounds__(256) void decode_combine_kernel(DecodeParams p) {
     if (t < D) store_out<T>(p.out, (size_t)bh * D + t, 0.f);
     return;
   }
+  // Few partials (one per lane at most, and kFew per thread): every load of the
+  // head is issued at once and the weights travel between lanes, so the merge
+  // costs one memory latency instead of two and one barrier instead of four.
+  constexpr int kFew = 16;
+  if (ns <= min(64, SUB * kFew)) {
+    const int lane = t & 63, c = t % D, sub = t / D;
+    const float* pl = part + (size_t)min(lane, ns - 1) * stride;
+    const float ml = pl[D], ll = pl[D + 1];
+    float x[kFew];
+#pragma unroll
+    for (int i = 0; i < kFew; ++i)
+      if (sub + i * SUB < ns) x[i] = part[(size_t)(sub + i * SUB) * stride + c];  // uniform per wave
+    float M = ml;
+    for (int sh = 32; sh > 0; sh >>= 1) M = fmaxf(M, __shfl_xor(M, sh));
+    const float Ms = (M == -INFINITY) ? 0.f : M;
+    const float w = lane < ns ? fast_exp2(ml - Ms) : 0.f;
+    float L = lane < ns ? ll * w : 0.f;
+    for (int sh = 32; sh > 0; sh >>= 1) L += __shfl_xor(L, sh);
+    float a = 0.f;
+#pragma unroll
+    for (int i = 0; i < kFew; ++i)
+      if (sub + i * SUB < ns) a = fmaf(x[i], __shfl(w, sub + i * SUB), a);
+    s_acc[sub][c] = a;
+    __syncthreads();
+    if (t < D) {
+      float o = 0.f;
+#pragma unroll
+      for (int j = 0; j < SUB; ++j) o += s_acc[j][t];
+      store_out<T>(p.out, (size_t)bh * D + t, L > 0.f ? o / L : 0.f);
+    }
+    return;
+  }
   float mloc = -INFINITY;
   for (int k = t; k < ns; k += 256) mloc = fmaxf(mloc, part[k * stride + D]);
   for (int sh = 32; sh > 0; sh >>= 1) mloc = fmaxf(mloc, __shfl_xor(mloc, sh));
@@ -943,7 +977,9 @@ hipError_t launch_t(const DecodeParams& p, hipStream_t st) {
   // Grouped heads over a 128-wide bf16 cache run on the matrix cores.
   constexpr bool kMfma = sizeof(T) == 2 && D == 128 && R >= 2;
   constexpr int lds = Ring<T, D, KEYS, NW>::BYTES;
-  static_assert(lds + NW * R * (D + 2) * 4 <= 160 * 1024, "LDS budget");
+  using RS = Ring<T, D, KEYS, NW>;
+  constexpr bool kMergeInRing = kMfma && R * D * 4 <= RS::NBUF * RS::SB;
+  static_assert(lds + (NW * R * (kMergeInRing ? 3 : D + 3) + 2 * R) * 4 <= 160 * 1024, "LDS budget");
   const void* kern;
   if constexpr (kMfma)
     kern = reinterpret_cast<const void*>(decode_mfma_kernel<R, PAGED, KEYS, NW>);
@@ -972,10 +1008,25 @@ hipError_t launch_t(const DecodeParams& p, hipStream_t st) {
   return e;
 }
 
+// Waves of a wide workgroup. Matrix cores: 8, whose rings keep three tiles each
+// in flight (16 waves have LDS for one each: batch 1, 12 heads on 2 groups, 512
+// rows 7.7 against 7.0 us). Vector ALU: 16 where the registers (128 each) and the
+// LDS allow, to overlap the waves' arithmetic (fp32, 8 heads x 64, 6 sequences: 6.2
+// against 7.1 us), else 8; 4 where not even those fit.
+template <typename T, int D, int R>
+constexpr int wide_waves() {
+  if (sizeof(T) == 2 && D == 128) return R >= 2 ? 8 : 16;
+  if (sizeof(T) == 4 && D == 128) return R <= 7 ? 8 : 4;
+  return R <= (sizeof(T) == 4 ? 4 : 2) ? 16 : 8;
+}
+
 template <typename T, int D, int R>
 hipError_t pick_layout(const DecodeParams& p, hipStream_t st) {
   constexpr int NW = 4;  // waves per workgroup
   const bool keys = p.kdata != nullptr;
+  if (p.wide && !keys)
+    return p.paged ? launch_t<T, D, R, true, false, wide_waves<T, D, R>()>(p, st)
+                   : launch_t<T, D, R, false, false, wide_waves<T, D, R>()>(p, st);
   if (p.paged)
     return keys ? launch_t<T, D, R, true, true, NW>(p, st) : launch_t<T, D, R, true, false, NW>(p, st);
   return keys ? launch_t<T, D, R, false, true, NW>(p, st) : launch_t<T, D, R, false, false, NW>(p, st);

@@ -52,6 +52,7 @@ struct DecodeParams {
   int num_blocks, max_blocks;
   int chunk;              // rows per split (multiple of 64)
   int S;                  // splits per sequence (at most kMaxSplits)
+  bool wide;              // 8 or 16 waves per workgroup instead of 4 (no keys)
   bool balanced;          // balanced mode: nwg workgroups share the tiles of all pairs evenly
   int nwg;                // workgroups in balanced mode (at most kMaxSplits)
   float scale_log2;       // scale * log2(e)

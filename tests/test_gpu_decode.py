@@ -541,3 +541,44 @@ def test_long_context_most_splits(lib, H, G):
     torch.cuda.synchronize()
     ref = K.keyless_decode(to64(q), to64(cache), lengths.numpy(), H, G)
     assert_parity(out, ref, torch.bfloat16, "long context")
+
+
+@pytest.mark.parametrize("dtype,B,H,G,d,L", [
+    (torch.bfloat16, 1, 12, 2, 128, 1000), (torch.bfloat16, 9, 32, 1, 128, 700),
+    (torch.bfloat16, 40, 4, 4, 128, 3000), (torch.bfloat16, 5, 8, 1, 64, 500),
+    (torch.bfloat16, 2, 12, 2, 128, 3000), (torch.float32, 3, 7, 1, 128, 1200),
+    (torch.float32, 1, 8, 1, 128, 5000), (torch.float32, 6, 8, 8, 64, 1900)])
+@pytest.mark.parametrize("paged", [False, True])
+def test_wide_workgroups(lib, dtype, B, H, G, d, L, paged):
+    """Each number of waves of the wide workgroups (one split, and fixed splits),
+    lengths from empty to full, as a decode and as a fused step (bit-equal to append
+    then decode, whose new row joins the same way)."""
+    if paged:
+        L = -(-L // 16) * 16
+    say(f"wide decode {dtype} B={B} H={H} G={G} d={d} L={L} paged={paged}")
+    rows = synth.normal((B, G, L, d), 151, 1, 1.0, dtype)
+    q = synth.normal((B, H, d), 151, 2, 1.0, dtype)
+    new = synth.normal((B, G, d), 151, 3, 1.0, dtype)
+    lengths = torch.tensor([(0, 1, 15, 17, L // 2, L - 1)[b % 6] if b else L - 1 for b in range(B)],
+                           dtype=torch.int32)
+
+    def cache():
+        if not paged:
+            return kb.ValueCache(rows.clone().to(DEV))
+        n = L // 16
+        table = torch.randperm(B * n, generator=torch.Generator().manual_seed(1)).to(torch.int32)
+        data = torch.zeros((B * n, G, 16, d), dtype=dtype)
+        data[table.long()] = rows.view(B, G, n, 16, d).permute(0, 2, 1, 3, 4).reshape(B * n, G, 16, d)
+        return kb.ValueCache(data.to(DEV), table.view(B, n).to(DEV))
+
+    vc = cache()
+    out = kb.keyless_decode(q.to(DEV), vc, lengths.to(DEV))
+    step = kb.keyless_decode_append(q.to(DEV), new.to(DEV), vc, lengths.to(DEV))
+    torch.cuda.synchronize()
+    assert_parity(out, K.keyless_decode(to64(q), to64(rows), lengths.numpy(), H, G), dtype, "decode")
+    ref = K.value_cache_append(to64(rows), to64(new)[:, None], lengths.numpy())
+    assert_parity(step, K.keyless_decode(to64(q), ref, lengths.numpy() + 1, H, G), dtype, "step")
+    other = cache()
+    kb.value_cache_append(other, new[:, None].contiguous().to(DEV), lengths.to(DEV))
+    torch.cuda.synchronize()
+    assert torch.equal(vc.data, other.data)
