@@ -989,15 +989,18 @@ hipError_t launch_prep(const BwdParams& p, hipStream_t st) {
 // fp32 partial sums. One workgroup per tile fills the chip only with many tiles;
 // a grouped layer has few, each with every head of its group to walk (12 heads on
 // 2 groups, 2 x 1000 tokens: 24 workgroups, 280 us). Three workgroups per CU even
-// out the causal tiles' lengths; a split of fewer than four pairs costs more in
-// partials than it saves. Forward + backward at a target of 1 / 512 / 768 / 1024
+// out the causal tiles' lengths; a split of fewer than four pairs (ten once every
+// CU has a tile) costs more in partials than it saves, and so does any split above
+// two tiles per CU. Forward + backward at a target of 1 / 512 / 768 / 1024
 // workgroups, us: 12 on 2 heads, 8192 tokens 2687 / 997 / 928 / 904, 2000 tokens
-// 664 / 156 / 166 / 168; 32 on 8, 6000 tokens 1655 / 1386 / 1183 / 1158.
+// 664 / 156 / 166 / 168; 32 on 8, 6000 tokens 1655 / 1386 / 1183 / 1158. One
+// workgroup per tile / split at 32 on 32 heads: 2400 tokens (416 tiles) 260 / 243,
+// 3000 (512) 342 / 339, 3500 (608) 429 / 438, 4200 (704) 555 / 589.
 int attn_bwd_splits(int B, int N, int H, int G) {
   const long tiles = (long)G * B * ((N + BKVD - 1) / BKVD);
   const long pairs = (long)(H / G) * ((N + kTileRows - 1) / kTileRows);  // of the heaviest tile
-  if (tiles == 0) return 1;
-  return (int)std::max(1L, std::min((768 + tiles - 1) / tiles, pairs / 4));
+  if (tiles == 0 || tiles > 512) return 1;
+  return (int)std::max(1L, std::min((768 + tiles - 1) / tiles, pairs / (tiles < 256 ? 4 : 10)));
 }
 
 bool attn_bwd_mfma_supported(const BwdParams& p) {
