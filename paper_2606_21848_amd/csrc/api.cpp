@@ -935,7 +935,7 @@ namespace {
 
 // Workspace of the matrix-core form of keyless_weight_gradients (bf16):
 // dQ = dQ~ W^R^T [M, H d_head]; the transposes X^T and [dQ^T ; dV^T] over the
-// padded token count Mp (the second buffer later holds Q = X W^Q); dQ~^T and
+// padded token count Mp; dQ~^T and
 // Q^T [H d_head, Mp]; W^Q^T [H d_head, d_model]; the fp32 partial sums of
 // dW^R over S token chunks [S, H, d_head, d_head].
 struct WgradLayout {
@@ -1018,11 +1018,11 @@ int keyless_weight_gradients(const void* x, const void* W_Q, const void* W_R, co
         return fail(KL_ERR_UNSUPPORTED, "%s: %s", who, why);
       return hip_status(kl::launch_gemm_bf16(a, st), who);
     };
+    kl::TransposeJobs jobs{};
     auto tr = [&](const void* src, long ld_src, long rows, long cols, void* dst, long ld_dst,
                   long rows_pad) {
-      return hip_status(kl::launch_transpose_bf16(src, ld_src, (int)rows, (int)cols, dst, ld_dst,
-                                                  (int)rows_pad, st),
-                        who);
+      jobs.job[jobs.count++] =
+          kl::TransposeJob{src, ld_src, (int)rows, (int)cols, dst, ld_dst, (int)rows_pad, 0};
     };
     // C (rows x cols) = A W^T over K, optionally batched over the heads (item
     // strides sA, sW, sC), columns below n_split to C0, the rest to C1.
@@ -1052,29 +1052,29 @@ int keyless_weight_gradients(const void* x, const void* W_Q, const void* W_R, co
     // dQ_h = dQ~_h W^R_h^T (W^R_h as stored is the [n][k] operand).
     if (dW_Q || dx)
       s = prod(dq_routed, NQ, dk, W_R, dk, dk * dk, dk, M, dk, dQm, NQ, dk, dk, dQm, NQ, H);
+    // Every transpose of the call, once dQ is there, in one launch.
+    if (dW_Q || dW_V) tr(x, d_model, M, d_model, xT, L.Mp, L.Mp);
+    if (dW_Q) tr(dQm, NQ, M, NQ, dT, L.Mp, L.Mp);
+    if (dW_V) tr(dv, NV, M, NV, dT + (size_t)NQ * L.Mp * 2, L.Mp, L.Mp);
+    if (dW_R) {
+      tr(W_Q, NQ, d_model, NQ, WQT, d_model, d_model);
+      tr(dq_routed, NQ, M, NQ, dqT, L.Mp, L.Mp);
+      // The padded token columns of Q^T (no rows: zeros).
+      tr(W_Q, NQ, 0, NQ, static_cast<uint16_t*>(QT) + M, L.Mp, L.Mp - M);
+    }
+    if (s == KL_OK) s = hip_status(kl::launch_transpose_bf16(jobs, st), who);
     if (s == KL_OK && (dW_Q || dW_V)) {
       // [dW^Q | dW^V] = X^T [dQ | dV], a contraction over the (padded) tokens.
-      s = tr(x, d_model, M, d_model, xT, L.Mp, L.Mp);
-      if (s == KL_OK && dW_Q) s = tr(dQm, NQ, M, NQ, dT, L.Mp, L.Mp);
-      if (s == KL_OK && dW_V) s = tr(dv, NV, M, NV, dT + (size_t)NQ * L.Mp * 2, L.Mp, L.Mp);
-      if (s == KL_OK) {
-        const char* Wt = dW_Q ? dT : dT + (size_t)NQ * L.Mp * 2;
-        const long cols = (dW_Q ? NQ : 0) + (dW_V ? NV : 0);
-        s = prod(xT, L.Mp, 0, Wt, L.Mp, 0, L.Mp, d_model, cols, dW_Q ? dW_Q : dW_V,
-                 dW_Q ? NQ : NV, 0, dW_Q ? NQ : cols, dW_V ? dW_V : dW_Q, NV, 1);
-      }
+      const char* Wt = dW_Q ? dT : dT + (size_t)NQ * L.Mp * 2;
+      const long cols = (dW_Q ? NQ : 0) + (dW_V ? NV : 0);
+      s = prod(xT, L.Mp, 0, Wt, L.Mp, 0, L.Mp, d_model, cols, dW_Q ? dW_Q : dW_V,
+               dW_Q ? NQ : NV, 0, dW_Q ? NQ : cols, dW_V ? dW_V : dW_Q, NV, 1);
     }
     if (s == KL_OK && dW_R) {
-      // Q = X W^Q (into the [dQ^T ; dV^T] buffer, whose product above has run:
-      // the stream orders them), Q^T and dQ~^T with zero token padding, then
-      // Eq. 5: dW^R_h = Q_h^T dQ~_h, a contraction over the tokens batched over
-      // the heads.
-      void* Qm = dT;  // [M, NQ]
-      s = tr(W_Q, NQ, d_model, NQ, WQT, d_model, d_model);
-      if (s == KL_OK)
-        s = prod(x, d_model, 0, WQT, d_model, 0, d_model, M, NQ, Qm, NQ, 0, NQ, Qm, NQ, 1);
-      if (s == KL_OK) s = tr(Qm, NQ, M, NQ, QT, L.Mp, L.Mp);
-      if (s == KL_OK) s = tr(dq_routed, NQ, M, NQ, dqT, L.Mp, L.Mp);
+      // Q^T = W^Q^T X^T straight in the layout of Eq. 5: dW^R_h = Q_h^T dQ~_h, a
+      // contraction over the tokens batched over the heads (the store's column
+      // split lies past the last token, on a whole four columns).
+      s = prod(WQT, d_model, 0, x, d_model, 0, d_model, NQ, M, QT, L.Mp, 0, (M + 3) / 4 * 4, QT, L.Mp, 1);
       if (s == KL_OK) {
         // Item (h, z): rows of head h, tokens of chunk z; fp32 partials, then
         // their sum in chunk order.

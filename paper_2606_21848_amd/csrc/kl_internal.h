@@ -161,11 +161,23 @@ hipError_t launch_gemm_bf16_packed(const void* A, int M, int K, long lda, const 
                                    hipStream_t stream);
 
 // dst[c][r] = src[r][c] for r < rows, c < cols (bf16); dst columns r in
-// [rows, rows_pad) are written as zeros. Row strides in elements; `batch`
-// matrices s_src and s_dst elements apart.
-hipError_t launch_transpose_bf16(const void* src, long ld_src, int rows, int cols, void* dst,
-                                 long ld_dst, int rows_pad, hipStream_t stream, int batch = 1,
-                                 long s_src = 0, long s_dst = 0);
+// [rows, rows_pad) are written as zeros. Row strides in elements; src 16-byte
+// aligned. Up to kMax such matrices in one launch.
+struct TransposeJob {
+  const void* src;
+  long ld_src;
+  int rows, cols;
+  void* dst;
+  long ld_dst;
+  int rows_pad;
+  int blocks;  // set by the launch
+};
+struct TransposeJobs {
+  static constexpr int kMax = 6;
+  TransposeJob job[kMax];
+  int count;
+};
+hipError_t launch_transpose_bf16(TransposeJobs& jobs, hipStream_t stream);
 
 // Packed projection weights: rows [0, H d) = (W^Q W^R per head)^T (or W^Q^T
 // when W_R is null), rows [H d, (H+G) d) = W^V^T; each row has d_model entries.
