@@ -94,7 +94,7 @@ int cache_capacity(const kl_value_cache* c) {
 //  - At most kSmallBatch sequences: split mode with splits sized from the
 //    capacity (see below).
 //  - Otherwise balanced mode: kBalancedWorkgroups workgroups (two per compute
-//    unit) take equal shares of the 16-row tiles of all pairs, whatever the
+//    unit; one wide one where that is faster) take equal shares of the 16-row tiles of all pairs, whatever the
 //    spread of lengths, and a merge kernel combines pairs that were shared.
 //    Used while the tile count fits comfortably in 32 bits; beyond that the
 //    cache is split into chunks of 8192 rows.
@@ -223,6 +223,7 @@ int decode_common(const void* q, const kl_value_cache* k_cache, const kl_value_c
   p.lengths = lengths;
   p.vnew = vnew;
   p.out = out;
+  p.paged = v_cache->layout == KL_PAGED;
   // Fixed splits that leave each CU at most one workgroup take wide ones too: half
   // or a quarter of the tiles per wave (batch 1, 12 heads on 2 groups, 2048 rows: 9.8
   // -> 8.9 us; with two workgroups per CU, 512 splits, 11.7 -> 13.5).
@@ -230,10 +231,16 @@ int decode_common(const void* q, const kl_value_cache* k_cache, const kl_value_c
                     (long)B * G * pl.S <= kComputeUnits);
   p.balanced = pl.balanced;
   p.nwg = kBalancedWorkgroups;
-  if (pl.balanced && R == 32 && !k_cache) {
-    // 32 heads merge 16 KiB per wave: one workgroup of 8 waves per CU instead of
-    // two of 4 halves the partials (latent decode, batch 32 x 16384 rows: 46.4 ->
-    // 41.2 us; 16 heads on 4 waves stay faster, 30.8 against 32.0).
+  if (pl.balanced && !k_cache && v_cache->dtype == KL_BF16 && v_cache->d_head == 128 &&
+      (R != 16 || p.paged)) {
+    // One wide workgroup per CU instead of two of 4 waves: half the segments, so
+    // half the merges and partials, with more tiles in flight where 16 waves run.
+    // Caches that do not fit the last-level cache, us (4 waves / wide): paged, 32
+    // heads on 8 groups, 64 x 1k to 32k rows 353 / 341; 12 on 2, 6 x 30000 23.5 / 20.9;
+    // 32 on 32, 7 x 6000 70.6 / 61.3; latent, 32 on 1, 32 x 16384 46.4 / 41.2; paged, 32
+    // on 2, 30 x 4000 24.5 / 22.7, but contiguous, 16 on 1, 20 x 16000 32.5 / 33.6. On
+    // the vector ALU with more than one row per lane group the merge of 16 waves costs
+    // more (fp32, 8 x 64, 20 x 6000: 31.7 / 35.6).
     p.wide = true;
     p.nwg = kComputeUnits;
   }
@@ -249,7 +256,6 @@ int decode_common(const void* q, const kl_value_cache* k_cache, const kl_value_c
   p.D = v_cache->d_head;
   p.R = R;
   p.dtype = v_cache->dtype;
-  p.paged = v_cache->layout == KL_PAGED;
   p.L_max = v_cache->L_max;
   p.block_shift = p.paged ? log2_exact(v_cache->block_size) : 0;
   p.num_blocks = v_cache->num_blocks;
