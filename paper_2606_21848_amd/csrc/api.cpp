@@ -137,6 +137,8 @@ DecodePlan plan_decode(const kl_value_cache* c, int B, int chunk_rows) {
   return pl;
 }
 
+long cache_row_bytes(const kl_value_cache* c) { return c->d_head * (long)elem_bytes(c->dtype); }
+
 // Whether one wide workgroup (8 or 16 waves) per (b, g) pair decodes the whole
 // capacity, without splits or a merge kernel. One CU streams about 64 KB a
 // microsecond, and the merge launch costs about 4 us: against the fixed splits of
@@ -149,7 +151,7 @@ DecodePlan plan_decode(const kl_value_cache* c, int B, int chunk_rows) {
 bool one_wide_split(const kl_value_cache* c, int B, int R) {
   const long pairs = (long)B * c->G;
   const bool valu = !(c->dtype == KL_BF16 && c->d_head == 128);
-  const long bytes = (long)cache_capacity(c) * c->d_head * (long)elem_bytes(c->dtype) * (valu ? R : 1);
+  const long bytes = cache_capacity(c) * cache_row_bytes(c) * (valu ? R : 1);
   if (bytes <= 0 || pairs >= kComputeUnits) return false;
   const long most = B <= kSmallBatch ? 256L << 10 : (pairs >= kComputeUnits / 2 ? 1024L << 10 : 512L << 10);
   return bytes <= most;
@@ -227,12 +229,19 @@ int decode_common(const void* q, const kl_value_cache* k_cache, const kl_value_c
   // Fixed splits that leave each CU at most one workgroup take wide ones too: half
   // or a quarter of the tiles per wave (batch 1, 12 heads on 2 groups, 2048 rows: 9.8
   // -> 8.9 us; with two workgroups per CU, 512 splits, 11.7 -> 13.5).
-  p.wide = wide || (!k_cache && chunk_rows == 0 && !pl.balanced && pl.S > 1 &&
-                    (long)B * G * pl.S <= kComputeUnits);
+  // One split per pair with every CU busy takes them for long caches (512 KiB per
+  // pair and more) on the vector ALU, whose arithmetic 4 waves do not hide, us (4
+  // waves / wide): fp32, 32 heads x 128, 10 x up to 8000 rows 154 / 130; fp32, 64 heads
+  // on 16 groups x 64, 20 x up to 4000 77.2 / 55.5; bf16, the same, 57.7 / 44.1. 128-wide
+  // bf16 rows keep 4: 32 heads, batch 8 x 4096 49 / 44.5 by itself, but 57.4 / 58.2 in a
+  // step behind its projections.
+  const bool bf16_128 = v_cache->dtype == KL_BF16 && v_cache->d_head == 128;
+  p.wide = wide || (!k_cache && chunk_rows == 0 && !pl.balanced &&
+                    (pl.S > 1 ? (long)B * G * pl.S <= kComputeUnits
+                              : !bf16_128 && cache_row_bytes(v_cache) * cache_capacity(v_cache) >= (512L << 10)));
   p.balanced = pl.balanced;
   p.nwg = kBalancedWorkgroups;
-  if (pl.balanced && !k_cache && v_cache->dtype == KL_BF16 && v_cache->d_head == 128 &&
-      (R != 16 || p.paged)) {
+  if (pl.balanced && !k_cache && bf16_128 && (R != 16 || p.paged)) {
     // One wide workgroup per CU instead of two of 4 waves: half the segments, so
     // half the merges and partials, with more tiles in flight where 16 waves run.
     // Caches that do not fit the last-level cache, us (4 waves / wide): paged, 32

@@ -547,7 +547,8 @@ def test_long_context_most_splits(lib, H, G):
     (torch.bfloat16, 1, 12, 2, 128, 1000), (torch.bfloat16, 9, 32, 1, 128, 700),
     (torch.bfloat16, 40, 4, 4, 128, 3000), (torch.bfloat16, 5, 8, 1, 64, 500),
     (torch.bfloat16, 2, 12, 2, 128, 3000), (torch.float32, 3, 7, 1, 128, 1200),
-    (torch.float32, 1, 8, 1, 128, 5000), (torch.float32, 6, 8, 8, 64, 1900)])
+    (torch.float32, 1, 8, 1, 128, 5000), (torch.float32, 6, 8, 8, 64, 1900),
+    (torch.float32, 8, 64, 32, 64, 2500)])
 @pytest.mark.parametrize("paged", [False, True])
 def test_wide_workgroups(lib, dtype, B, H, G, d, L, paged):
     """Each number of waves of the wide workgroups (one split, and fixed splits),
