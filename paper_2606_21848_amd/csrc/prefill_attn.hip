@@ -573,7 +573,8 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bf16_split_kernel(AttnParams
   if (grp == 0) {
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) {
-      s_ml[wave][qb * 16 + fr][0] = osum[qb][0] > 0.f ? m[qb] : -INFINITY;
+      // A sum of zero: this wave saw none of the query's rows (a NaN must stay one).
+      s_ml[wave][qb * 16 + fr][0] = osum[qb][0] == 0.f ? -INFINITY : m[qb];
       s_ml[wave][qb * 16 + fr][1] = osum[qb][0];
     }
   }
@@ -592,7 +593,7 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bf16_split_kernel(AttnParams
     }
     if (p.lse && wave == 0 && grp == 0 && q0 + row < p.N)
       p.lse[((size_t)b * p.H + h) * p.N + q0 + row] = (mm + __log2f(l)) * 0.69314718055994531f;
-    const float f = osum[qb][0] > 0.f ? fast_exp2(m[qb] - mm) / l : 0.f;
+    const float f = osum[qb][0] == 0.f ? 0.f : fast_exp2(m[qb] - mm) / l;
 #pragma unroll
     for (int db = 0; db < DB; ++db) WaveSums<D>::put(ring, row, 4 * db + grp, o[db][qb] * f);
   }
