@@ -260,9 +260,9 @@ hipError_t launch_e(GemmF32Params& p, bool vec, int batch, hipStream_t st) {
   auto tiles = [&](int T) {
     return (long)((p.N + T - 1) / T + (p.Nd + T - 1) / T) * ((p.M + T - 1) / T) * batch;
   };
-  // The largest tile that fills the 256 CUs: one 128-wide tile each (two waves
-  // per SIMD do not pay for half the reuse), two 64-wide ones (a training layer of
-  // 1400 tokens at d_model 1024: 469 us, against 490 with one per CU).
+  // The largest tile that fills the 256 CUs: 128-wide from one per CU on (from two
+  // on: the same), 64-wide from two (a training layer of 1400 tokens at d_model 1024:
+  // 469 us, against 490 from one and 479 with 32-wide tiles only).
   if (tiles(128) >= 256) return launch_t<E, 128, 16>(p, vec, batch, st);
   if (tiles(64) >= 512) return launch_t<E, 64, 32>(p, vec, batch, st);
   return launch_t<E, 32, 64>(p, vec, batch, st);
