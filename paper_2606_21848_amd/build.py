@@ -39,8 +39,10 @@ def hipcc() -> str:
 # Per-source code-generation options. The GEMM's k-step wants all of its LDS
 # fragment reads in flight before the MFMAs (one wait instead of one per
 # fragment pair); LLVM's iterative ILP scheduler produces that schedule. The
-# attention's scores are finite or -inf, never NaN: without NaN semantics its
-# maxima become v_max3_f32 with no canonicalising moves.
+# attention's scores of finite inputs are finite or -inf, never NaN: without NaN
+# semantics its maxima become v_max3_f32 with no canonicalising moves. A NaN input
+# still gives NaN rows (arithmetic keeps it); a test of a value that may be NaN
+# compares its bits there.
 PER_SOURCE = {
     "gemm_bf16.hip": ["-mllvm", "-amdgpu-sched-strategy=iterative-ilp"],
     "prefill_attn.hip": ["-fno-honor-nans"],

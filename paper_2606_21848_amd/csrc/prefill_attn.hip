@@ -569,12 +569,15 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bf16_split_kernel(AttnParams
   }
 
   // Merge: each wave's (m, l) of its queries, then the waves' outputs scaled to
-  // the common reference, added in wave order.
+  // the common reference, added in wave order. A sum of zero: the wave saw none of
+  // the query's rows. A NaN sum must reach the log-sum-exp as one, and this file is
+  // compiled without NaN semantics (a float compare may be turned into one that is
+  // false for NaN), so both tests compare bits; sums are never -0.
+  auto unseen = [](float l) { return __float_as_uint(l) == 0u; };
   if (grp == 0) {
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) {
-      // A sum of zero: this wave saw none of the query's rows (a NaN must stay one).
-      s_ml[wave][qb * 16 + fr][0] = osum[qb][0] == 0.f ? -INFINITY : m[qb];
+      s_ml[wave][qb * 16 + fr][0] = unseen(osum[qb][0]) ? -INFINITY : m[qb];
       s_ml[wave][qb * 16 + fr][1] = osum[qb][0];
     }
   }
@@ -588,12 +591,12 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bf16_split_kernel(AttnParams
     for (int w = 1; w < NW; ++w) mm = fmaxf(mm, s_ml[w][row][0]);
 #pragma unroll
     for (int w = 0; w < NW; ++w) {
-      const float mw = s_ml[w][row][0];
-      l += mw == -INFINITY ? 0.f : s_ml[w][row][1] * fast_exp2(mw - mm);
+      const float lw = s_ml[w][row][1];
+      l += unseen(lw) ? 0.f : lw * fast_exp2(s_ml[w][row][0] - mm);
     }
     if (p.lse && wave == 0 && grp == 0 && q0 + row < p.N)
       p.lse[((size_t)b * p.H + h) * p.N + q0 + row] = (mm + __log2f(l)) * 0.69314718055994531f;
-    const float f = osum[qb][0] == 0.f ? 0.f : fast_exp2(m[qb] - mm) / l;
+    const float f = unseen(osum[qb][0]) ? 0.f : fast_exp2(m[qb] - mm) / l;
 #pragma unroll
     for (int db = 0; db < DB; ++db) WaveSums<D>::put(ring, row, 4 * db + grp, o[db][qb] * f);
   }

@@ -218,3 +218,30 @@ def test_prefill_long_sequence_sampled(lib):
     assert_parity(v[0], Vref, torch.bfloat16, "values")
     assert_parity(out[0, rows], Orows, torch.bfloat16, "sampled rows")
     assert torch.isfinite(out.float()).all()
+
+
+@pytest.mark.parametrize("where", ["query", "value"])
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("B,N,H,G,dk", [(1, 100, 2, 1, 64), (2, 77, 4, 4, 128), (1, 517, 12, 2, 128),
+                                        (8, 400, 16, 16, 64), (8, 400, 16, 16, 128)])
+def test_nan_rows_keep_their_log_sum_exp(lib, B, N, H, G, dk, causal, where):
+    """A query that sees a NaN (its own, or one of a value row) gets NaN outputs and
+    a NaN log-sum-exp, the others a finite log-sum-exp that agrees with the oracle:
+    from the form whose waves share a query's values (the small shapes, the NaN in
+    one wave's rows only) and from the form of whole query tiles (B = 8)."""
+    say(f"NaN rows B={B} N={N} H={H} G={G} dk={dk} causal={causal} {where}")
+    at = 40  # a row of the second 32-row value tile
+    q = synth.normal((B, N, H, dk), 26, 1, 1.0)
+    v = synth.normal((B, N, G, dk), 26, 2, 1.0)
+    want = K.attention_logsumexp(to64(q), to64(v), H, G, dk, causal=causal)
+    (q if where == "query" else v)[:, at, :, 3] = float("nan")
+    rows = np.arange(N)
+    hit = rows == at if where == "query" else (rows >= at if causal else rows >= 0)
+    out, lse = kb.keyless_attention_forward(q.to(DEV), v.to(DEV), causal=causal)
+    torch.cuda.synchronize()
+    lse, out = to64(lse), to64(out)
+    assert np.isnan(lse[:, :, hit]).all()
+    assert np.isnan(out[:, hit]).all()
+    if not hit.all():
+        # A score is off by at most 2^-9 tau sum |q v| (q~ rounded once more).
+        assert np.abs(lse[:, :, ~hit] - want[:, :, ~hit]).max() <= 2e-2
