@@ -334,7 +334,8 @@ int keyless_decode_project(const void* x, const void* packed, int B, int d_model
  *   scale    0 selects 1/sqrt(d_head) (lambda = 1 in the Section 3 weight)
  *   out      [B, H, d_head], cache dtype. lengths[b] == 0 gives a zero row.
  *   ws       at least keyless_decode_workspace_size(...) bytes (may be 0, then
- *            ws may be NULL). Calls that run at the same time must not share it.
+ *            ws may be NULL), also where the form that runs uses none of it.
+ *            Calls that run at the same time must not share it.
  * Each cached value tile is read from HBM once and used both for the scores
  * and for the weighted sum. Work split (the built-in choice): a contiguous
  * cache with at least 256 (b, group) pairs, or one with little cache per pair
@@ -398,7 +399,7 @@ int keyless_decode_chunked(const void* q_routed, const kl_value_cache* cache,
 /* Workspace bytes for keyless_decode_chunked / standard_decode_chunked with
  * these arguments (chunk_rows 0 for keyless_decode / standard_decode): fp32
  * partial rows (d_head + 2 floats per head and split) plus, in the shared-tile
- * mode, a plan of B + 3 ints; 0 when no merge is needed. Host-only; depends on
+ * mode, a plan of B + 3 ints; 0 for a capacity of one split. Host-only; depends on
  * the descriptor's layout and capacity, not on the lengths. */
 size_t keyless_decode_workspace_size(const kl_value_cache* cache, int B, int H, int chunk_rows);
 

@@ -206,8 +206,6 @@ int decode_common(const void* q, const kl_value_cache* k_cache, const kl_value_c
     return fail(KL_ERR_INVALID_ARG, "%s: chunk_rows=%d must be a multiple of 64", who, chunk_rows);
   if (B == 0) return KL_OK;
   DecodePlan pl = plan_decode(v_cache, B, chunk_rows);
-  const bool wide = !k_cache && chunk_rows == 0 && one_wide_split(v_cache, B, R);
-  if (wide) pl = DecodePlan{(cache_capacity(v_cache) + 63) / 64 * 64, 1, false};
   if (pl.S > kl::kMaxSplits)
     return fail(KL_ERR_UNSUPPORTED, "%s: %d splits exceed the maximum of %d (use larger chunks)",
                 who, pl.S, kl::kMaxSplits);
@@ -216,6 +214,10 @@ int decode_common(const void* q, const kl_value_cache* k_cache, const kl_value_c
     return fail(KL_ERR_WORKSPACE, "%s: workspace of %zu bytes needed, %zu given", who, need, ws_bytes);
   if (need && !aligned16(ws))
     return fail(KL_ERR_INVALID_ARG, "%s: workspace must be 16-byte aligned", who);
+  // The workspace is the plan's whichever form runs: what a call accepts does not
+  // depend on where the forms' lines lie.
+  const bool wide = !k_cache && chunk_rows == 0 && one_wide_split(v_cache, B, R);
+  if (wide) pl = DecodePlan{(cache_capacity(v_cache) + 63) / 64 * 64, 1, false};
 
   kl::DecodeParams p{};
   p.q = q;

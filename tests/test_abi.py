@@ -92,6 +92,27 @@ def test_small_batch_split_plan(lib):
     assert lib.keyless_decode_workspace_size(ctypes.byref(p), 1, 12, 0) == _split_bytes(1, 12, 8)
 
 
+def test_decode_workspace_is_asked_for_whichever_form_runs(lib):
+    """A short, missing or misaligned workspace is refused wherever the size function
+    asks for one, also for caches small enough that one workgroup per pair decodes
+    them without partials, in every decode entry."""
+    caches = [cache(G=2, L_max=1024), cache(G=1, L_max=100), cache(G=16, L_max=4096),
+              cache(G=8, L_max=1500, d=64, dtype=kb.KL_F32),
+              cache(G=8, layout=kb.KL_PAGED, nb=200, mb=12)]
+    for c in caches:
+        for B in (5, 14):
+            H = 2 * c.G
+            need = lib.keyless_decode_workspace_size(ctypes.byref(c), B, H, 0)
+            assert need > 0
+            expect(lib, decode(lib, c, B=B, H=H, ws_bytes=need - 1), kb.KL_ERR_WORKSPACE, "workspace")
+            expect(lib, decode(lib, c, B=B, H=H, ws=None), kb.KL_ERR_WORKSPACE, "workspace")
+            expect(lib, decode(lib, c, B=B, H=H, ws=ctypes.c_void_p(0x100008)),
+                   kb.KL_ERR_INVALID_ARG, "aligned")
+            st = lib.keyless_decode_append(FAKE, FAKE, ctypes.byref(c), FAKE, B, H, 0.0, FAKE, None, 0,
+                                           None)
+            expect(lib, st, kb.KL_ERR_WORKSPACE, "workspace")
+
+
 def test_decode_rejects_bad_arguments(lib):
     expect(lib, decode(lib, cache(), q=None), kb.KL_ERR_INVALID_ARG, "non-NULL")
     expect(lib, decode(lib, cache(d=96)), kb.KL_ERR_UNSUPPORTED, "d_head 96")
