@@ -93,9 +93,9 @@ int cache_capacity(const kl_value_cache* c) {
 //    workgroup per pair streams its whole cache and writes the output directly.
 //  - At most kSmallBatch sequences: split mode with splits sized from the
 //    capacity (see below).
-//  - Otherwise balanced mode: kBalancedWorkgroups workgroups (two per compute
-//    unit; one wide one where that is faster) take equal shares of the 16-row tiles of all pairs, whatever the
-//    spread of lengths, and a merge kernel combines pairs that were shared.
+//  - Otherwise balanced mode: kBalancedWorkgroups workgroups (two per compute unit;
+//    for few pairs one wide one) take equal shares of the 16-row tiles of all pairs,
+//    whatever the spread of lengths, and a merge kernel combines pairs that were shared.
 //    Used while the tile count fits comfortably in 32 bits; beyond that the
 //    cache is split into chunks of 8192 rows.
 struct DecodePlan {
@@ -107,6 +107,7 @@ constexpr int kComputeUnits = 256;
 constexpr int kBalancedWorkgroups = 2 * kComputeUnits;
 constexpr int kSmallBatch = 4;                        // sequences decoded with fixed splits
 constexpr long kSplitWorkgroups = 2 * kComputeUnits;  // their target split count
+constexpr long kWidePairs = 64;                       // most (b, g) pairs that 256 wide workgroups share
 
 DecodePlan plan_decode(const kl_value_cache* c, int B, int chunk_rows) {
   const int cap = cache_capacity(c);
@@ -243,15 +244,17 @@ int decode_common(const void* q, const kl_value_cache* k_cache, const kl_value_c
                               : !bf16_128 && cache_row_bytes(v_cache) * cache_capacity(v_cache) >= (512L << 10)));
   p.balanced = pl.balanced;
   p.nwg = kBalancedWorkgroups;
-  if (pl.balanced && !k_cache && bf16_128 && (R != 16 || p.paged)) {
-    // One wide workgroup per CU instead of two of 4 waves: half the segments, so
-    // half the merges and partials, with more tiles in flight where 16 waves run.
-    // Caches that do not fit the last-level cache, us (4 waves / wide): paged, 32
-    // heads on 8 groups, 64 x 1k to 32k rows 353 / 341; 12 on 2, 6 x 30000 23.5 / 20.9;
-    // 32 on 32, 7 x 6000 70.6 / 61.3; latent, 32 on 1, 32 x 16384 46.4 / 41.2; paged, 32
-    // on 2, 30 x 4000 24.5 / 22.7, but contiguous, 16 on 1, 20 x 16000 32.5 / 33.6. On
-    // the vector ALU with more than one row per lane group the merge of 16 waves costs
-    // more (fp32, 8 x 64, 20 x 6000: 31.7 / 35.6).
+  if (pl.balanced && !k_cache && bf16_128 && R >= 2 && (long)B * G <= kWidePairs) {
+    // One wide workgroup per CU instead of two of 4 waves: half the segments, so half
+    // the merges and partials; but a workgroup meets its pairs one after another
+    // with nothing beside it on the CU, so pairs that are short against a workgroup's
+    // share (which only the device knows) cost their latencies in a row. us (4 waves
+    // / wide): latent, 32 heads on 1, 32 x 16384 39.9 / 36.3; 16 on 1, 20 x 16384 30.3 /
+    // 28.3; paged, 6 on 1, 12 x 32768 30.1 / 27.6; 48 pairs of 8 heads, up to 1500 of
+    // 16384 rows 18.9 / 17.3; at 64 pairs equal within 2% for ragged lengths; 128 pairs
+    // of 8 heads, up to 1500 rows 26.2 / 37.7; paged, 32 heads on 8, 64 x up to 1000
+    // 36.8 / 47.5. With one head per group (vector ALU, 16 waves) 32 pairs of up to
+    // 1500 rows take 12.0 / 14.4.
     p.wide = true;
     p.nwg = kComputeUnits;
   }
