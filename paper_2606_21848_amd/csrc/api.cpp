@@ -232,16 +232,23 @@ int decode_common(const void* q, const kl_value_cache* k_cache, const kl_value_c
   // Fixed splits that leave each CU at most one workgroup take wide ones too: half
   // or a quarter of the tiles per wave (batch 1, 12 heads on 2 groups, 2048 rows: 9.8
   // -> 8.9 us; with two workgroups per CU, 512 splits, 11.7 -> 13.5).
-  // One split per pair with every CU busy takes them for long caches (512 KiB per
-  // pair and more) on the vector ALU, whose arithmetic 4 waves do not hide, us (4
-  // waves / wide): fp32, 32 heads x 128, 10 x up to 8000 rows 154 / 130; fp32, 64 heads
-  // on 16 groups x 64, 20 x up to 4000 77.2 / 55.5; bf16, the same, 57.7 / 44.1. 128-wide
-  // bf16 rows keep 4: 32 heads, batch 8 x 4096 49 / 44.5 by itself, but 57.4 / 58.2 in a
-  // step behind its projections.
+  // One split per pair takes them where that is one workgroup per CU (256 pairs) of
+  // 512 KiB of capacity and more, on the vector ALU, where the heads of a group have
+  // arithmetic that 4 waves do not hide. Time of 4 waves over wide, 256 pairs of up
+  // to 4096 (bf16 and fp32 x 64) rows; all full, 1 to 1500, 300, 64 rows each:
+  //   fp32, 4 heads x 128 1.41 1.41 1.29 1.01    bf16, 4 heads x 64 1.35 1.24 0.98 0.96
+  //   fp32, 4 heads x 64  1.43 1.42 1.11 0.80    bf16, 2 heads x 64 1.20 1.23 0.86 0.73
+  //   fp32, 1 head x 64   0.99 1.27 1.07 0.93    bf16, 1 head x 64  1.09 1.24 0.95 0.86
+  // With more pairs than CUs two workgroups of 4 waves share a CU and win (fp32, 4
+  // heads x 128, 800 pairs of 1200 rows 127 / 137 us; 32 to 100 KiB per pair: 0.6 to
+  // 0.9). 128-wide bf16 rows keep 4: 32 heads, batch 8 x 4096 49 / 44.5 us by itself,
+  // but 57.4 / 58.2 in a step behind its projections.
   const bool bf16_128 = v_cache->dtype == KL_BF16 && v_cache->d_head == 128;
+  const bool valu_heads = !bf16_128 && R >= (v_cache->dtype == KL_BF16 ? 3 : 2);
   p.wide = wide || (!k_cache && chunk_rows == 0 && !pl.balanced &&
                     (pl.S > 1 ? (long)B * G * pl.S <= kComputeUnits
-                              : !bf16_128 && cache_row_bytes(v_cache) * cache_capacity(v_cache) >= (512L << 10)));
+                              : valu_heads && (long)B * G <= kComputeUnits &&
+                                    cache_row_bytes(v_cache) * cache_capacity(v_cache) >= (512L << 10)));
   p.balanced = pl.balanced;
   p.nwg = kBalancedWorkgroups;
   if (pl.balanced && !k_cache && bf16_128 && R >= 2 && (long)B * G <= kWidePairs) {
