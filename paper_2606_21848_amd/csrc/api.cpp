@@ -231,7 +231,10 @@ int decode_common(const void* q, const kl_value_cache* k_cache, const kl_value_c
   p.paged = v_cache->layout == KL_PAGED;
   // Fixed splits that leave each CU at most one workgroup take wide ones too: half
   // or a quarter of the tiles per wave (batch 1, 12 heads on 2 groups, 2048 rows: 9.8
-  // -> 8.9 us; with two workgroups per CU, 512 splits, 11.7 -> 13.5).
+  // -> 8.9 us; with two workgroups per CU, 512 splits, 11.7 -> 13.5), but not over
+  // 64-wide bf16 rows, 8 of which share a load: merging the lanes of each of 8 or 16
+  // waves costs more than the shorter walk saves (2 heads per group, 8 splits of 256
+  // rows 8.9 / 9.9; 8 heads 16.0 / 16.9; 1 and 4 heads equal).
   // One split per pair takes them where that is one workgroup per CU (256 pairs) of
   // 512 KiB of capacity and more, on the vector ALU, where the heads of a group have
   // arithmetic that 4 waves do not hide. Time of 4 waves over wide, 256 pairs of up
@@ -244,9 +247,10 @@ int decode_common(const void* q, const kl_value_cache* k_cache, const kl_value_c
   // 0.9). 128-wide bf16 rows keep 4: 32 heads, batch 8 x 4096 49 / 44.5 us by itself,
   // but 57.4 / 58.2 in a step behind its projections.
   const bool bf16_128 = v_cache->dtype == KL_BF16 && v_cache->d_head == 128;
+  const bool bf16_64 = v_cache->dtype == KL_BF16 && v_cache->d_head == 64;
   const bool valu_heads = !bf16_128 && R >= (v_cache->dtype == KL_BF16 ? 3 : 2);
   p.wide = wide || (!k_cache && chunk_rows == 0 && !pl.balanced &&
-                    (pl.S > 1 ? (long)B * G * pl.S <= kComputeUnits
+                    (pl.S > 1 ? !bf16_64 && (long)B * G * pl.S <= kComputeUnits
                               : valu_heads && (long)B * G <= kComputeUnits &&
                                     cache_row_bytes(v_cache) * cache_capacity(v_cache) >= (512L << 10)));
   p.balanced = pl.balanced;
