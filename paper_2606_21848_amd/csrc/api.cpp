@@ -142,20 +142,33 @@ long cache_row_bytes(const kl_value_cache* c) { return c->d_head * (long)elem_by
 
 // Whether one wide workgroup (8 or 16 waves) per (b, g) pair decodes the whole
 // capacity, without splits or a merge kernel. One CU streams about 64 KB a
-// microsecond, and the merge launch costs about 4 us: against the fixed splits of
-// at most kSmallBatch sequences the line is at 256 KiB per pair (12 heads on 2
-// groups, 1000 rows: 8.9 / 13.6 us, 2000 rows: 12.7 / 10.1), against the balanced
-// mode at 512 KiB (64 pairs: 15.2 / 18.5 us), and at 1 MiB with half the CUs busy
-// (224 pairs: 37.2 / 44.7; 64 pairs: 24.9 / 21.3). On the vector ALU each head of a
-// group adds its own arithmetic per row (fp32, 4 heads per group, 12 x 2000 rows
-// of 64: 22.4 / 17.9), so there a group counts with its heads.
+// microsecond, and the merge launch costs about 4 us. On the vector ALU each head of
+// a group adds its own arithmetic per row (fp32, 4 heads per group, 12 x 2000 rows
+// of 64: 22.4 / 17.9 us), so there a group counts with its heads. Times below: wide /
+// the other form, us, whole capacities.
+//  - Against the fixed splits of at most kSmallBatch sequences the line is at 256 KiB
+//    per pair (12 heads on 2 groups, 1000 rows: 8.9 / 13.6, 2000 rows: 12.7 / 10.1);
+//    not over 64-wide rows of bf16 (32 KiB 4.9 / 4.5, 256 KiB 10.2 / 8.2) or of 3 or 4
+//    fp32 heads (8 KiB 6.1 / 5.0, 64 KiB 6.7 / 6.3), where the other form is one
+//    workgroup without a merge as well and 16 waves have little to share.
+//  - Against the balanced mode the line rises with the pairs, as its 512 workgroups
+//    have more to merge: below 16 pairs 384 KiB (6 pairs, 8 heads per group, 512 KiB
+//    15.0 / 14.0), then 512 KiB (64 pairs 15.2 / 18.5), from 128 pairs 768 KiB (128
+//    pairs, 1 MiB 24.9 / 23.8), from 192 pairs 1 MiB (224 pairs 37.2 / 44.7).
+//  - With one head per group the 16 waves' merge weighs more (24 pairs, 400 KiB 12.7 /
+//    10.7; 128 pairs, 800 KiB 23.4 / 21.8; 240 pairs, 1 MiB, ragged 33.1 / 30.5): 256 KiB,
+//    from 128 pairs 512, from 192 pairs 768; 64-wide fp32 rows, with the least
+//    arithmetic per byte, keep the lines above (48 pairs, 512 KiB, ragged 8.2 / 11.4).
 bool one_wide_split(const kl_value_cache* c, int B, int R) {
   const long pairs = (long)B * c->G;
-  const bool valu = !(c->dtype == KL_BF16 && c->d_head == 128);
+  const bool bf16 = c->dtype == KL_BF16, w64 = c->d_head == 64;
+  const bool valu = !(bf16 && !w64);
   const long bytes = cache_capacity(c) * cache_row_bytes(c) * (valu ? R : 1);
-  if (bytes <= 0 || pairs >= kComputeUnits) return false;
-  const long most = B <= kSmallBatch ? 256L << 10 : (pairs >= kComputeUnits / 2 ? 1024L << 10 : 512L << 10);
-  return bytes <= most;
+  auto within = [&](long kib) { return bytes <= kib << 10; };
+  if (cache_capacity(c) <= 0 || pairs >= kComputeUnits) return false;
+  if (B <= kSmallBatch) return within(256) && !(w64 && (bf16 || R == 3 || R == 4));
+  if (R == 1 && !(w64 && !bf16)) return within(pairs >= 192 ? 768 : pairs >= 128 ? 512 : 256);
+  return within(pairs >= 192 ? 1024 : pairs >= 128 ? 768 : pairs >= 16 ? 512 : 384);
 }
 
 // Workspace: split partials (acc[d], m, l) per (b, h, split), none with a
@@ -255,7 +268,8 @@ int decode_common(const void* q, const kl_value_cache* k_cache, const kl_value_c
                                     cache_row_bytes(v_cache) * cache_capacity(v_cache) >= (512L << 10)));
   p.balanced = pl.balanced;
   p.nwg = kBalancedWorkgroups;
-  if (pl.balanced && !k_cache && bf16_128 && R >= 2 && (long)B * G <= kWidePairs) {
+  if (pl.balanced && !k_cache && bf16_128 && R >= 2 && (long)B * G <= kWidePairs &&
+      (long)B * G * cache_capacity(v_cache) >= kComputeUnits * 128L) {
     // One wide workgroup per CU instead of two of 4 waves: half the segments, so half
     // the merges and partials; but a workgroup meets its pairs one after another
     // with nothing beside it on the CU, so pairs that are short against a workgroup's
@@ -265,7 +279,9 @@ int decode_common(const void* q, const kl_value_cache* k_cache, const kl_value_c
     // 16384 rows 18.9 / 17.3; at 64 pairs equal within 2% for ragged lengths; 128 pairs
     // of 8 heads, up to 1500 rows 26.2 / 37.7; paged, 32 heads on 8, 64 x up to 1000
     // 36.8 / 47.5. With one head per group (vector ALU, 16 waves) 32 pairs of up to
-    // 1500 rows take 12.0 / 14.4.
+    // 1500 rows take 12.0 / 14.4. And a capacity of less than one 16-row tile per wave
+    // (128 rows per workgroup) leaves waves idle (6 pairs x 2048 rows, 16 heads each 15.9 /
+    // 17.8).
     p.wide = true;
     p.nwg = kComputeUnits;
   }
