@@ -621,15 +621,33 @@ hipError_t launch_attn_qb(const AttnParams& p, hipStream_t st) {
   return hipGetLastError();
 }
 
+// Whether the form whose waves share the value tiles is the faster one. It pays
+// where the whole-tile form leaves CUs idle (fewer than 300 of its workgroups) and
+// its own 32-row blocks still run nearly all at once: two per CU at D = 128 (64 KiB of
+// LDS each), about four at D = 64. Past that a long causal chain of tiles, which
+// the waves cut to a quarter, is worth more rounds only with few heads; unmasked, where
+// all blocks are equal, more rounds never pay at D = 128, nor does a single value tile.
+// Whole tiles / split, us, heads x rows, without the fp32 output:
+//   D 128, causal: 128 x 128 10.9 / 9.8, 128 x 192 13.6 / 15.1, 64 x 384 17.5 / 15.8, 64 x
+//     640 22.4 / 25.6, 32 x 1300 36.7 / 33.1, 48 x 1000 32.2 / 34.3, 12 x 2200 52.6 / 29.5
+//   D 128, unmasked: 48 x 320 12.6 / 11.7, 48 x 384 13.7 / 16.8, 128 x 128 9.1 / 9.7, 16 x
+//     1700 35.2 / 41.5
+//   D 64, causal: 96 x 320 11.3 / 10.7, 192 x 192 10.5 / 10.9, 256 x 128 8.7 / 9.2
+//   D 64, unmasked: 96 x 160 8.1 / 7.6, 96 x 192 7.6 / 8.7, 24 x 768 14.0 / 12.6, 48 x 640
+//     13.0 / 14.1
+bool few_query_tiles(const AttnParams& p) {
+  const long heads = (long)p.H * p.B, bq = p.causal ? 192 : 128;
+  const long blocks = heads * ((p.N + 31) / 32);
+  if (heads * ((p.N + bq - 1) / bq) >= 300) return false;
+  if (p.causal)
+    return p.D == 64 ? heads <= 96 || blocks <= 768
+                     : blocks <= 512 || heads <= 32 || (heads <= 64 && blocks <= 1024);
+  return p.Nk > 64 && ((heads <= 96 && blocks <= 512) || (p.D == 64 && heads <= 24));
+}
+
 template <int D>
 hipError_t launch_attn(const AttnParams& p, hipStream_t st) {
-  // Fewer 192-row (128-row) workgroups than about one per CU: the split form. At
-  // 12 heads, causal, whole prefill in us (this form / the other): 517 tokens (36
-  // workgroups) 19.4 / 29.2, 2000 (132) 43.5 / 64.0, 4000 (252) 100 / 116, 8000
-  // (504) 287 / 238; 32 heads, 1000 (192) 84.6 / 90.2, 2000 (352) 161 / 156; 32
-  // heads, 500 queries on 4000 values (128) 177 / 197.
-  const int bq = p.causal ? 192 : 128;
-  if ((long)p.H * p.B * ((p.N + bq - 1) / bq) < 300) {
+  if (few_query_tiles(p)) {
     constexpr int lds = 4 * 2 * AttnTile<D, 32>::BYTES;
     hipLaunchKernelGGL(attn_bf16_split_kernel<D>, dim3(p.H, (p.N + 31) / 32, p.B), dim3(kThreads), lds,
                        st, p);
