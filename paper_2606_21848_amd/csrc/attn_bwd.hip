@@ -938,15 +938,27 @@ hipError_t launch_simple(const BwdParams& p, hipStream_t st) {
   return hipGetLastError();
 }
 
+// Whether dQ~ takes the form whose waves share the value tiles: where the 128-row
+// form leaves CUs idle (fewer than 300 workgroups), a query has more than one
+// 64-row value tile, and the 32-row blocks run one per CU, or few heads have long
+// chains of tiles. dQ~ and dV together, whole tiles / split, us, heads x rows:
+//   D 128, causal: 24 x 512 48.5 / 42.9, 24 x 1000 70.1 / 66.5, 32 x 384 43.0 / 39.4, 32 x
+//     640 59.7 / 61.2, 48 x 320 36.9 / 37.6, 128 x 192 36.0 / 43.3
+//   D 128, unmasked: 16 x 1300 94.4 / 91.2, 32 x 1000 94.3 / 98.1, 48 x 512 58.4 / 61.3
+//   D 64, causal: 48 x 512 38.4 / 36.5, 64 x 320 28.9 / 30.0
+//   one 64-row value tile: 0.3 to 1.5 us more
+template <int D>
+bool dq_few_query_tiles(const BwdParams& p) {
+  const long heads = (long)p.H * p.B;
+  if (p.N <= 64 || heads * ((p.N + BQD - 1) / BQD) >= 300) return false;
+  return heads * ((p.N + 31) / 32) <= 256 || heads <= (D == 128 && !p.causal ? 24 : 32);
+}
+
 template <int D>
 hipError_t launch_mfma(const BwdParams& p, hipStream_t st) {
   using TL = AttnTile<D, kTileRows>;
-  // Fewer 128-row workgroups than about one per CU: the split form. Forward +
-  // backward, us (this form / the other): 12 heads, 1000 tokens (96 workgroups)
-  // 62.8 / 75.6, 3000 (288) 213 / 231; 32 heads, 1000 (256) 111 / 112, 1500 (384)
-  // 172 / 169.
   constexpr int split_lds = 4 * 2 * AttnTile<D, 32>::BYTES;
-  if (p.out_f32 && (long)p.H * p.B * ((p.N + BQD - 1) / BQD) < 300)
+  if (p.out_f32 && dq_few_query_tiles<D>(p))
     hipLaunchKernelGGL(bwd_dq_split_kernel<D>, dim3(p.H, (p.N + 31) / 32, p.B), dim3(kThreads),
                        split_lds, st, p);
   else if (p.out_f32)
