@@ -255,10 +255,12 @@ int keyless_attention_forward(const void* q_routed, const void* v, int B, int N,
  *   and dP in an extra sweep over the values (rowsum(dO * O) over the bf16
  *   output would carry its rounding into every dP - rowsum);
  *   dq_routed [B, N, H, d_head], dv [B, N, G, d_head]; all 16-byte aligned.
- *   ws, ws_bytes  keyless_attention_backward_workspace_size(B, N, H) bytes: the
+ *   ws, ws_bytes  keyless_attention_backward_workspace_size_for(...) bytes: the
  *                 per-row rowsum(dO * O), B*H*N floats rounded up to 256 bytes
- *                 (the least that is accepted), and room for fp32 partial sums
- *                 of dv, which let bf16 calls with few value tiles fill the chip
+ *                 (the least that is accepted), and for bf16 calls with few value
+ *                 tiles room for the fp32 partial sums of dv that let them fill
+ *                 the chip (at most 120 MiB). _workspace_size(B, N, H) is enough
+ *                 for every G, d_head and dtype
  * Self-attention only (the value rows are the query rows). bf16 with d_head 64
  * or 128 runs on MFMA (P and dS rounded to bf16 for the products, fp32
  * accumulation); fp32 on the vector ALU. Every output element is written once
@@ -270,6 +272,8 @@ int keyless_attention_backward(const void* q_routed, const void* v, const void* 
                                int d_head, int causal, float scale, kl_dtype dtype, void* dq_routed,
                                void* dv, void* ws, size_t ws_bytes, void* stream);
 size_t keyless_attention_backward_workspace_size(int B, int N, int H);
+size_t keyless_attention_backward_workspace_size_for(int B, int N, int H, int G, int d_head,
+                                                     kl_dtype dtype);
 
 /*
  * keyless_weight_gradients - the rest of the backward pass through the

@@ -27,8 +27,8 @@ EXPORTS = (
     "keyless_cross_attention_packed",
     "keyless_latent_decode", "keyless_latent_decode_workspace_size",
     "keyless_attention_forward", "keyless_attention_backward",
-    "keyless_attention_backward_workspace_size", "keyless_weight_gradients",
-    "keyless_weight_gradients_workspace_size",
+    "keyless_attention_backward_workspace_size", "keyless_attention_backward_workspace_size_for",
+    "keyless_weight_gradients", "keyless_weight_gradients_workspace_size",
     "keyless_decode_project", "keyless_decode", "keyless_decode_chunked", "keyless_decode_workspace_size",
     "keyless_decode_append", "keyless_decode_noalloc",
     "value_cache_append", "standard_decode", "standard_decode_chunked",
@@ -91,6 +91,7 @@ def load(path: str = LIB_PATH):
         "keyless_attention_backward": (i, [vp, vp, vp, vp, vp, vp, i, i, i, i, i, i, f, i, vp,
                                            vp, vp, sz, vp]),
         "keyless_attention_backward_workspace_size": (sz, [i, i, i]),
+        "keyless_attention_backward_workspace_size_for": (sz, [i, i, i, i, i, i]),
         "keyless_weight_gradients": (i, [vp, vp, vp, vp, vp, vp, i, i, i, i, i, i, i, vp, vp, vp,
                                          vp, vp, sz, vp]),
         "keyless_weight_gradients_workspace_size": (sz, [i, i, i, i, i, i, i]),
@@ -475,7 +476,7 @@ def keyless_attention_backward(q_routed: torch.Tensor, v: torch.Tensor, out: tor
     if dv is None:
         dv = torch.empty_like(v)
     if workspace is None:
-        n = int(_lib.keyless_attention_backward_workspace_size(B, N, H))
+        n = int(_lib.keyless_attention_backward_workspace_size_for(B, N, H, G, dk, _dt(q_routed)))
         workspace = torch.empty(max(n, 256), dtype=torch.uint8, device=q_routed.device)
     _check(_lib.keyless_attention_backward(_ptr(q_routed), _ptr(v), _ptr(out), _ptr(out_f32),
                                            _ptr(dout), _ptr(lse),

@@ -913,11 +913,11 @@ int keyless_attention_forward(const void* q_routed, const void* v, int B, int N,
 
 namespace {
 
-// The row sums that every call needs, and the most that the partial sums of dV
-// take for some G and d_head (a workspace without room for them is accepted).
+// The row sums that every call needs, and the partial sums of dV that a call with
+// these arguments uses (a workspace without room for them is accepted).
 size_t bwd_rows_bytes(int B, int N, int H) { return align256((size_t)B * H * N * sizeof(float)); }
-size_t bwd_part_bytes(int B, int N, int H, int G, int d_head) {
-  const int S = kl::attn_bwd_splits(B, N, H, G);
+size_t bwd_part_bytes(int B, int N, int H, int G, int d_head, kl_dtype dtype) {
+  const int S = dtype == KL_BF16 ? kl::attn_bwd_splits(B, N, H, G) : 1;
   return S > 1 ? (size_t)S * B * N * G * d_head * sizeof(float) : 0;
 }
 
@@ -926,9 +926,16 @@ size_t bwd_part_bytes(int B, int N, int H, int G, int d_head) {
 size_t keyless_attention_backward_workspace_size(int B, int N, int H) {
   if (B < 0 || N < 0 || H <= 0) return 0;
   size_t part = 0;
-  for (int G = 1; G <= H; ++G)
-    if (H % G == 0) part = std::max(part, bwd_part_bytes(B, N, H, G, 128));
+  for (int f = 1; (long)f * f <= H; ++f)
+    if (H % f == 0)
+      for (int G : {f, H / f}) part = std::max(part, bwd_part_bytes(B, N, H, G, 128, KL_BF16));
   return bwd_rows_bytes(B, N, H) + align256(part);
+}
+
+size_t keyless_attention_backward_workspace_size_for(int B, int N, int H, int G, int d_head,
+                                                     kl_dtype dtype) {
+  if (B < 0 || N < 0 || H <= 0 || G <= 0 || H % G != 0 || d_head <= 0) return 0;
+  return bwd_rows_bytes(B, N, H) + align256(bwd_part_bytes(B, N, H, G, d_head, dtype));
 }
 
 int keyless_attention_backward(const void* q_routed, const void* v, const void* out,
@@ -970,7 +977,7 @@ int keyless_attention_backward(const void* q_routed, const void* v, const void* 
   p.scale_log2 = p.scale * kLog2e;
   p.dtype = dtype;
   p.S = 1;
-  const size_t part = bwd_part_bytes(B, N, H, G, d_head);
+  const size_t part = bwd_part_bytes(B, N, H, G, d_head, dtype);
   if (part > 0 && ws_bytes >= need + part && aligned16(ws)) {
     p.S = kl::attn_bwd_splits(B, N, H, G);
     p.part = reinterpret_cast<float*>(static_cast<char*>(ws) + need);

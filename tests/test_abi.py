@@ -113,6 +113,33 @@ def test_decode_workspace_is_asked_for_whichever_form_runs(lib):
             expect(lib, st, kb.KL_ERR_WORKSPACE, "workspace")
 
 
+def test_backward_workspace_is_what_the_call_uses(lib):
+    """The query with every argument asks for dv's partial sums only where the call
+    splits dv (bf16 with few value tiles), never for more than 120 MiB of them; the
+    one that knows only B, N and H covers every G, d_head and dtype."""
+    size, size_for = (lib.keyless_attention_backward_workspace_size,
+                      lib.keyless_attention_backward_workspace_size_for)
+
+    def rows(B, N, H):
+        return -(-B * N * H * 4 // 256) * 256
+
+    for B, N, H in ((1, 8192, 32), (1, 100, 4), (2, 1000, 12), (4, 517, 30), (1, 1, 1), (64, 192, 8),
+                    (1, 32768, 64), (3, 0, 8), (0, 64, 8)):
+        for G in (g for g in range(1, H + 1) if H % g == 0):
+            assert size_for(B, N, H, G, 128, kb.KL_F32) == rows(B, N, H)
+            for d in (64, 128):
+                n = size_for(B, N, H, G, d, kb.KL_BF16)
+                assert rows(B, N, H) <= n <= size(B, N, H) <= rows(B, N, H) + (120 << 20)
+    # One value tile per head and more than two per CU: nothing to split.
+    assert size_for(1, 8192, 32, 32, 128, kb.KL_BF16) == rows(1, 8192, 32)
+    # Two groups of 2 x 1000 tokens, 24 value tiles: the largest tile's 96 (head,
+    # query tile) pairs go to 24 workgroups, each with partial sums.
+    assert size_for(2, 1000, 12, 2, 128, kb.KL_BF16) == rows(2, 1000, 12) + 24 * 2 * 1000 * 2 * 128 * 4
+    # The largest head count there is (a prime): no walk over all its candidates.
+    assert size(1, 1, 2 ** 31 - 1) >= rows(1, 1, 2 ** 31 - 1)
+    assert size_for(1, 64, 8, 3, 128, kb.KL_BF16) == size_for(1, 64, 0, 1, 128, kb.KL_BF16) == 0
+
+
 def test_decode_rejects_bad_arguments(lib):
     expect(lib, decode(lib, cache(), q=None), kb.KL_ERR_INVALID_ARG, "non-NULL")
     expect(lib, decode(lib, cache(d=96)), kb.KL_ERR_UNSUPPORTED, "d_head 96")
