@@ -261,9 +261,10 @@ int keyless_attention_forward(const void* q_routed, const void* v, int B, int N,
  *                 tiles room for the fp32 partial sums of dv that let them fill
  *                 the chip (at most 120 MiB). _workspace_size(B, N, H) is enough
  *                 for every G, d_head and dtype
- * Self-attention only (the value rows are the query rows). bf16 with d_head 64
- * or 128 runs on MFMA (P and dS rounded to bf16 for the products, fp32
- * accumulation); fp32 on the vector ALU. Every output element is written once
+ * Self-attention only (the value rows are the query rows). Both types run on MFMA,
+ * bf16 with P and dS rounded to bf16 for the products and fp32 accumulation, fp32
+ * with fp32 products; bf16 takes rows of fewer than 2^27 elements (H * d_head;
+ * longer ones are KL_ERR_UNSUPPORTED). Every output element is written once
  * (no atomics): results are deterministic.
  */
 int keyless_attention_backward(const void* q_routed, const void* v, const void* out,

@@ -977,6 +977,8 @@ int keyless_attention_backward(const void* q_routed, const void* v, const void* 
   p.scale_log2 = p.scale * kLog2e;
   p.dtype = dtype;
   p.S = 1;
+  if (const char* why = dtype == KL_BF16 ? kl::attn_bwd_bf16_unsupported(p) : nullptr)
+    return fail(KL_ERR_UNSUPPORTED, "%s: %s", who, why);
   const size_t part = bwd_part_bytes(B, N, H, G, d_head, dtype);
   if (part > 0 && ws_bytes >= need + part && aligned16(ws)) {
     p.S = kl::attn_bwd_splits(B, N, H, G);

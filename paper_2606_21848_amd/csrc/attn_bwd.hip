@@ -17,9 +17,7 @@
 // output would put that rounding into every dP - Dd) and then bwd_dv_kernel
 // (one workgroup per 192-row value tile and value group; query and dO tiles of
 // every head of the group stream through LDS, the values stay in registers).
-// fp32 has matrix-core kernels of its own (attn_f32.hip); what none of them
-// takes: bwd_prep_kernel (Dd from the fp32 output, else from the output) and
-// two vector-ALU kernels. No
+// fp32 has kernels of its own (attn_f32.hip). No
 // atomics: every output element is written once, by one lane.
 //
 // bf16 runs on v_mfma_f32_16x16x32_bf16 with the forward's operand layouts:
@@ -59,45 +57,6 @@ __device__ __forceinline__ void copy_dword_to_lds(const void* gbase, uint32_t vo
                :
                : "v"(voff), "s"(gbase), "s"(lds)
                : "memory", "m0");
-}
-
-template <typename T>
-__device__ __forceinline__ float ldx(const T* p, size_t i) {
-  if constexpr (sizeof(T) == 2) return __uint_as_float((uint32_t)p[i] << 16);
-  else return p[i];
-}
-template <typename T>
-__device__ __forceinline__ void stx(T* p, size_t i, float v) {
-  if constexpr (sizeof(T) == 2) p[i] = __builtin_bit_cast(uint16_t, (__bf16)v);
-  else p[i] = v;
-}
-
-// Dd[b, h, q] = sum_d dO[b, q, h, d] O[b, q, h, d] for the vector-ALU kernels;
-// 16 lanes per row. O is the forward's fp32 output when given (TO = float, row
-// stride H D), else `out`.
-template <typename TO, typename T, int D>
-__global__ __launch_bounds__(256) void bwd_prep_kernel(BwdParams p) {
-  const long rows = (long)p.B * p.N * p.H;
-  const long row = (long)blockIdx.x * 16 + threadIdx.x / 16;
-  const int j = threadIdx.x % 16;
-  float s = 0.f;
-  int b = 0, q = 0, h = 0;
-  if (row < rows) {
-    h = (int)(row % p.H);
-    const long bq = row / p.H;
-    b = (int)(bq / p.N);
-    q = (int)(bq % p.N);
-    const TO* o = p.out_f32 ? reinterpret_cast<const TO*>(p.out_f32) + ((size_t)bq * p.H + h) * D
-                            : reinterpret_cast<const TO*>(p.out) + (size_t)bq * p.o_stride + (size_t)h * D;
-    const T* g = reinterpret_cast<const T*>(p.dout) + (size_t)bq * p.o_stride + (size_t)h * D;
-#pragma unroll
-    for (int c = j; c < D; c += 16) s = fmaf(ldx(o, c), ldx(g, c), s);
-  }
-  s += __shfl_xor(s, 8);
-  s += __shfl_xor(s, 4);
-  s += __shfl_xor(s, 2);
-  s += __shfl_xor(s, 1);
-  if (row < rows && j == 0) p.Dd[((size_t)b * p.H + h) * p.N + q] = s;
 }
 
 // ---------------------------------------------------------------------------
@@ -814,130 +773,6 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_dv_kernel(BwdParams p) {
   }
 }
 
-// ---------------------------------------------------------------------------
-// Vector ALU, one thread per query row (dQ~) or value row (dV)
-// ---------------------------------------------------------------------------
-
-template <typename T, int D>
-__global__ __launch_bounds__(64) void bwd_dq_simple_kernel(BwdParams p) {
-  const int i0 = blockIdx.x * 64;
-  const int h = blockIdx.y, b = blockIdx.z;
-  const int g = h / (p.H / p.G);
-  const int i = i0 + threadIdx.x;
-  const bool live = i < p.N;
-  const T* Q = reinterpret_cast<const T*>(p.q);
-  const T* V = reinterpret_cast<const T*>(p.v);
-  const T* G = reinterpret_cast<const T*>(p.dout);
-  __shared__ float sV[64][D];
-  float q[D], go[D], acc[D];
-  float l2 = 0.f, dd = 0.f;
-  if (live) {
-    l2 = p.lse[((size_t)b * p.H + h) * p.N + i] * kLog2e;
-    dd = p.Dd[((size_t)b * p.H + h) * p.N + i];
-  }
-#pragma unroll
-  for (int c = 0; c < D; ++c) {
-    q[c] = live ? ldx(Q, ((size_t)b * p.N + i) * p.q_stride + (size_t)h * D + c) * p.scale_log2 : 0.f;
-    go[c] = live ? ldx(G, ((size_t)b * p.N + i) * p.o_stride + (size_t)h * D + c) : 0.f;
-    acc[c] = 0.f;
-  }
-  const int jend = p.causal ? min(p.N, i0 + 64) : p.N;
-  for (int j0 = 0; j0 < jend; j0 += 64) {
-    __syncthreads();
-    for (int e = threadIdx.x; e < 64 * D; e += 64) {
-      const int jj = e / D, c = e % D, j = j0 + jj;
-      sV[jj][c] = j < p.N ? ldx(V, ((size_t)b * p.N + j) * p.v_stride + (size_t)g * D + c) : 0.f;
-    }
-    __syncthreads();
-    const int jmax = min(64, (p.causal ? min(i + 1, p.N) : p.N) - j0);
-    for (int jj = 0; jj < jmax; ++jj) {
-      float s = 0.f, dp = 0.f;
-#pragma unroll
-      for (int c = 0; c < D; ++c) {
-        s = fmaf(q[c], sV[jj][c], s);
-        dp = fmaf(go[c], sV[jj][c], dp);
-      }
-      const float ds = fast_exp2(s - l2) * (dp - dd);
-#pragma unroll
-      for (int c = 0; c < D; ++c) acc[c] = fmaf(ds, sV[jj][c], acc[c]);
-    }
-  }
-  if (live) {
-    T* out = reinterpret_cast<T*>(p.dq);
-#pragma unroll
-    for (int c = 0; c < D; ++c)
-      stx(out, ((size_t)b * p.N + i) * p.dq_stride + (size_t)h * D + c, acc[c] * p.scale);
-  }
-}
-
-template <typename T, int D>
-__global__ __launch_bounds__(64) void bwd_dv_simple_kernel(BwdParams p) {
-  const int j0 = blockIdx.x * 64;
-  const int g = blockIdx.y, b = blockIdx.z;
-  const int R = p.H / p.G;
-  const int j = j0 + threadIdx.x;
-  const bool live = j < p.N;
-  const T* Q = reinterpret_cast<const T*>(p.q);
-  const T* V = reinterpret_cast<const T*>(p.v);
-  const T* G = reinterpret_cast<const T*>(p.dout);
-  __shared__ float sQ[32][D];
-  __shared__ float sG[32][D];
-  __shared__ float sL[32], sD[32];
-  float v[D], acc[D];
-#pragma unroll
-  for (int c = 0; c < D; ++c) {
-    v[c] = live ? ldx(V, ((size_t)b * p.N + j) * p.v_stride + (size_t)g * D + c) : 0.f;
-    acc[c] = 0.f;
-  }
-  const int ibeg = p.causal ? j0 : 0;
-  for (int h = g * R; h < g * R + R; ++h) {
-    for (int i0 = ibeg; i0 < p.N; i0 += 32) {
-      __syncthreads();
-      for (int e = threadIdx.x; e < 32 * D; e += 64) {
-        const int ii = e / D, c = e % D, i = i0 + ii;
-        const bool ok = i < p.N;
-        sQ[ii][c] = ok ? ldx(Q, ((size_t)b * p.N + i) * p.q_stride + (size_t)h * D + c) : 0.f;
-        sG[ii][c] = ok ? ldx(G, ((size_t)b * p.N + i) * p.o_stride + (size_t)h * D + c) : 0.f;
-      }
-      if (threadIdx.x < 32) {
-        const int i = i0 + threadIdx.x;
-        const bool ok = i < p.N;
-        sL[threadIdx.x] = ok ? p.lse[((size_t)b * p.H + h) * p.N + i] * kLog2e : 0.f;
-        sD[threadIdx.x] = ok ? p.Dd[((size_t)b * p.H + h) * p.N + i] : 0.f;
-      }
-      __syncthreads();
-      const int imax = min(32, p.N - i0);
-      for (int ii = 0; ii < imax; ++ii) {
-        if (p.causal && i0 + ii < j) continue;
-        float s = 0.f, dp = 0.f;
-#pragma unroll
-        for (int c = 0; c < D; ++c) {
-          s = fmaf(sQ[ii][c], v[c], s);
-          dp = fmaf(sG[ii][c], v[c], dp);
-        }
-        const float pr = fast_exp2(s * p.scale_log2 - sL[ii]);
-        const float ds = pr * (dp - sD[ii]) * p.scale;
-#pragma unroll
-        for (int c = 0; c < D; ++c) acc[c] = fmaf(pr, sG[ii][c], fmaf(ds, sQ[ii][c], acc[c]));
-      }
-    }
-  }
-  if (live) {
-    T* out = reinterpret_cast<T*>(p.dv);
-#pragma unroll
-    for (int c = 0; c < D; ++c) stx(out, ((size_t)b * p.N + j) * p.dv_stride + (size_t)g * D + c, acc[c]);
-  }
-}
-
-template <typename T, int D>
-hipError_t launch_simple(const BwdParams& p, hipStream_t st) {
-  hipLaunchKernelGGL((bwd_dq_simple_kernel<T, D>), dim3((p.N + 63) / 64, p.H, p.B), dim3(64), 0, st, p);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((bwd_dv_simple_kernel<T, D>), dim3((p.N + 63) / 64, p.G, p.B), dim3(64), 0, st, p);
-  return hipGetLastError();
-}
-
 // Whether dQ~ takes the form whose waves share the value tiles: where the 128-row
 // form leaves CUs idle (fewer than 300 workgroups), a query has more than one
 // 64-row value tile, and the 32-row blocks run one per CU, or few heads have long
@@ -982,19 +817,6 @@ hipError_t launch_mfma(const BwdParams& p, hipStream_t st) {
   return launch_sum_partials_bf16(p.part, p.S, (size_t)p.B * p.N * p.G * D, p.dv, st);
 }
 
-template <typename TO, typename T>
-hipError_t launch_prep_t(const BwdParams& p, hipStream_t st) {
-  const long rows = (long)p.B * p.N * p.H;
-  const dim3 grid((unsigned)((rows + 15) / 16));
-  if (p.D == 128) hipLaunchKernelGGL((bwd_prep_kernel<TO, T, 128>), grid, dim3(256), 0, st, p);
-  else hipLaunchKernelGGL((bwd_prep_kernel<TO, T, 64>), grid, dim3(256), 0, st, p);
-  return hipGetLastError();
-}
-template <typename T>
-hipError_t launch_prep(const BwdParams& p, hipStream_t st) {
-  return p.out_f32 ? launch_prep_t<float, T>(p, st) : launch_prep_t<T, T>(p, st);
-}
-
 }  // namespace
 
 // Splits of each dV tile's (head, query tile) pairs over workgroups, each with
@@ -1015,30 +837,22 @@ int attn_bwd_splits(int B, int N, int H, int G) {
   return (int)std::max(1L, std::min((768 + tiles - 1) / tiles, pairs / (tiles < 256 ? 4 : 10)));
 }
 
-bool attn_bwd_mfma_supported(const BwdParams& p) {
-  return p.dtype == KL_BF16 && (p.D == 64 || p.D == 128) && p.q_stride % 8 == 0 &&
-         p.v_stride % 8 == 0 && p.o_stride % 8 == 0 && p.dq_stride % 4 == 0 &&
-         p.dv_stride % 4 == 0 && (size_t)p.v_stride * 2 * 8 < (1u << 31) &&
-         (size_t)p.q_stride * 2 * 8 < (1u << 31) && (size_t)p.o_stride * 2 * 8 < (1u << 31);
+const char* attn_bwd_bf16_unsupported(const BwdParams& p) {
+  // The copies to LDS add up to 8 rows to a base in 32-bit byte offsets.
+  const long limit = 1L << 27;
+  if (p.q_stride >= limit || p.v_stride >= limit || p.o_stride >= limit)
+    return "bf16 rows of H * d_head elements must be shorter than 2^27";
+  return nullptr;
 }
 
 hipError_t launch_attention_backward(const BwdParams& p, hipStream_t st) {
   if (p.B == 0 || p.N == 0) return hipSuccess;
   if (p.D != 64 && p.D != 128) return hipErrorInvalidValue;
-  // Dd: on the matrix cores from the fp32 output when there is one (in the dQ~
-  // kernel's prologue, which publishes it for the dV kernel), else from P and
-  // dP in the dQ~ kernel's first sweep; on the vector ALU from the output (the
-  // prep kernel).
-  if (attn_bwd_f32_supported(p)) return launch_attention_backward_f32(p, st);
-  const bool mfma = attn_bwd_mfma_supported(p);
-  if (!mfma) {
-    hipError_t e = p.dtype == KL_BF16 ? launch_prep<uint16_t>(p, st) : launch_prep<float>(p, st);
-    if (e != hipSuccess) return e;
-  }
-  if (mfma) return p.D == 128 ? launch_mfma<128>(p, st) : launch_mfma<64>(p, st);
-  if (p.dtype == KL_BF16)
-    return p.D == 128 ? launch_simple<uint16_t, 128>(p, st) : launch_simple<uint16_t, 64>(p, st);
-  return p.D == 128 ? launch_simple<float, 128>(p, st) : launch_simple<float, 64>(p, st);
+  if (p.dtype == KL_F32) return launch_attention_backward_f32(p, st);
+  if (attn_bwd_bf16_unsupported(p)) return hipErrorInvalidValue;
+  // Dd: from the fp32 output when there is one (in the dQ~ kernel's prologue, which
+  // publishes it for the dV kernel), else from P and dP in its first sweep.
+  return p.D == 128 ? launch_mfma<128>(p, st) : launch_mfma<64>(p, st);
 }
 
 }  // namespace kl

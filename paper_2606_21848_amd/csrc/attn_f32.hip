@@ -23,6 +23,8 @@
 // the LDS copy of the block, row pitch D + 4 floats so that the four lane
 // groups hit distinct banks.
 
+#include <algorithm>
+
 #include "kl_device.h"
 #include "kl_internal.h"
 
@@ -230,8 +232,8 @@ template <int D, int NW>
 __global__ __launch_bounds__(NW * 64, 2) void bwd_dq_f32_kernel(BwdParams p) {
   constexpr int S = D / 16;
   extern __shared__ __attribute__((aligned(16))) float lds_f32[];
-  const int nq = (p.N + 15) / 16;
-  const int q0 = (p.causal ? nq - 1 - (int)blockIdx.y : (int)blockIdx.y) * 16;
+  const int nq = (p.N + 15) / 16, blk = p.block0 + blockIdx.y;
+  const int q0 = (p.causal ? nq - 1 - blk : blk) * 16;
   const int h = blockIdx.x, b = blockIdx.z, kg = h / (p.H / p.G);
   const int lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -297,7 +299,7 @@ template <int D, int NW>
 __global__ __launch_bounds__(NW * 64, 2) void bwd_dv_f32_kernel(BwdParams p) {
   constexpr int S = D / 16;
   extern __shared__ __attribute__((aligned(16))) float lds_f32[];
-  const int kv0 = blockIdx.y * 16;  // block 0 is the heaviest under the causal mask
+  const int kv0 = (p.block0 + blockIdx.y) * 16;  // block 0 is the heaviest under the causal mask
   const int kg = blockIdx.x, b = blockIdx.z, R = p.H / p.G;
   const int lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -364,6 +366,7 @@ __global__ __launch_bounds__(NW * 64, 2) void bwd_dv_f32_kernel(BwdParams p) {
 // Waves per workgroup: eight share a block's work (two per SIMD at the kernels'
 // registers); the results of all are merged once.
 constexpr int kNW = 8;
+constexpr int kMaxGridY = 65535;
 
 template <class K, class P>
 hipError_t launch(K kern, const P& p, dim3 grid, int lds, std::atomic<uint32_t>& done, hipStream_t st) {
@@ -383,11 +386,19 @@ hipError_t launch_fwd(const AttnParams& p, hipStream_t st) {
 template <int D>
 hipError_t launch_bwd(const BwdParams& p, hipStream_t st) {
   static std::atomic<uint32_t> done_q{0}, done_v{0};
-  hipError_t e = launch(bwd_dq_f32_kernel<D, kNW>, p, dim3(p.H, (p.N + 15) / 16, p.B),
-                        kNW * Block<D>::FLOATS * 4, done_q, st);
+  // A grid takes 65535 row blocks; above a million rows both kernels run in several
+  // launches. dV reads the Dd of every query, so all of dQ~ runs first.
+  const int nblk = (p.N + 15) / 16;
+  auto all = [&](auto kern, int heads, int lds, std::atomic<uint32_t>& done) {
+    hipError_t e = hipSuccess;
+    BwdParams q = p;
+    for (q.block0 = 0; q.block0 < nblk && e == hipSuccess; q.block0 += kMaxGridY)
+      e = launch(kern, q, dim3(heads, std::min(nblk - q.block0, kMaxGridY), p.B), lds, done, st);
+    return e;
+  };
+  const hipError_t e = all(bwd_dq_f32_kernel<D, kNW>, p.H, kNW * Block<D>::FLOATS * 4, done_q);
   if (e != hipSuccess) return e;
-  return launch(bwd_dv_f32_kernel<D, kNW>, p, dim3(p.G, (p.N + 15) / 16, p.B),
-                2 * kNW * Block<D>::FLOATS * 4, done_v, st);
+  return all(bwd_dv_f32_kernel<D, kNW>, p.G, 2 * kNW * Block<D>::FLOATS * 4, done_v);
 }
 
 bool aligned(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
@@ -397,20 +408,13 @@ bool aligned(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0;
 bool attn_f32_supported(const AttnParams& p) {
   return p.dtype == KL_F32 && (p.D == 64 || p.D == 128) && p.Nk > 0 && p.q_stride % 4 == 0 &&
          p.v_stride % 4 == 0 && p.o_stride % 4 == 0 && aligned(p.q) && aligned(p.v) &&
-         aligned(p.out) && aligned(p.out_f32) && (p.N + 15) / 16 <= 65535;
+         aligned(p.out) && aligned(p.out_f32) && (p.N + 15) / 16 <= kMaxGridY;
 }
 
 hipError_t launch_attention_f32(const AttnParams& p, hipStream_t st) {
   if (p.N == 0 || p.B == 0) return hipSuccess;
   if (p.causal && p.Nk != p.N) return hipErrorInvalidValue;
   return p.D == 128 ? launch_fwd<128>(p, st) : launch_fwd<64>(p, st);
-}
-
-bool attn_bwd_f32_supported(const BwdParams& p) {
-  return p.dtype == KL_F32 && (p.D == 64 || p.D == 128) && p.q_stride % 4 == 0 &&
-         p.v_stride % 4 == 0 && p.o_stride % 4 == 0 && p.dq_stride % 4 == 0 &&
-         p.dv_stride % 4 == 0 && aligned(p.q) && aligned(p.v) && aligned(p.dout) && aligned(p.dq) &&
-         aligned(p.dv) && (p.N + 15) / 16 <= 65535;
 }
 
 hipError_t launch_attention_backward_f32(const BwdParams& p, hipStream_t st) {

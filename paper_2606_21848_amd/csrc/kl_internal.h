@@ -240,19 +240,20 @@ struct BwdParams {
   kl_dtype dtype;
   int S;             // splits of the dV sums (bf16 MFMA), 1 for none
   float* part;       // their fp32 partial sums [S, B, N, G, D]
+  int block0;        // first 16-row block of this launch (fp32)
 };
 int attn_bwd_splits(int B, int N, int H, int G);
-bool attn_bwd_mfma_supported(const BwdParams& p);
+// nullptr when the bf16 backward takes the call, else the reason it does not.
+const char* attn_bwd_bf16_unsupported(const BwdParams& p);
 hipError_t launch_attention_backward(const BwdParams& p, hipStream_t stream);
 
 // bf16 MFMA flash-style keyless attention (d_head 64 or 128).
 bool attn_bf16_supported(const AttnParams& p);
 hipError_t launch_prefill_attention(const AttnParams& p, hipStream_t stream);
 // fp32 MFMA attention (d_head 64 or 128, 16-byte aligned operands, at least one
-// value row) and its backward.
+// value row) and its backward (16-byte aligned operands, whole heads as strides).
 bool attn_f32_supported(const AttnParams& p);
 hipError_t launch_attention_f32(const AttnParams& p, hipStream_t stream);
-bool attn_bwd_f32_supported(const BwdParams& p);
 hipError_t launch_attention_backward_f32(const BwdParams& p, hipStream_t stream);
 // VALU attention for what the kernels above do not take.
 hipError_t launch_prefill_attention_simple(const AttnParams& p, hipStream_t stream);

@@ -140,6 +140,14 @@ def test_backward_workspace_is_what_the_call_uses(lib):
     assert size_for(1, 64, 8, 3, 128, kb.KL_BF16) == size_for(1, 64, 0, 1, 128, kb.KL_BF16) == 0
 
 
+def test_backward_refuses_rows_past_its_offsets(lib):
+    """bf16 rows of 2^27 elements and more (the copies' 32-bit offsets)."""
+    for H, G, d in ((1 << 20, 1, 128), (1 << 21, 1 << 21, 64)):
+        st = lib.keyless_attention_backward(FAKE, FAKE, FAKE, None, FAKE, FAKE, 1, 1, H, G, d, 1, 0.0,
+                                            kb.KL_BF16, FAKE, FAKE, FAKE, 1 << 40, None)
+        expect(lib, st, kb.KL_ERR_UNSUPPORTED, "2^27")
+
+
 def test_decode_rejects_bad_arguments(lib):
     expect(lib, decode(lib, cache(), q=None), kb.KL_ERR_INVALID_ARG, "non-NULL")
     expect(lib, decode(lib, cache(d=96)), kb.KL_ERR_UNSUPPORTED, "d_head 96")

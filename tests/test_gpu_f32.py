@@ -90,9 +90,36 @@ def test_attention_f32(lib, causal, B, N, H, G, dk):
     assert_parity(dv, rv, F32, "dV", 1e-2, scale)
 
 
+def test_attention_backward_f32_above_one_grid(lib):
+    """More 16-row blocks than a grid takes (65535): both kernels run in several
+    launches. Rows on both sides of the seam, the first and the last ones against
+    their sums in 64 bits (lse, out and dout are inputs: any finite values do). A
+    sum of n terms of either sign is off by about sqrt(n) 2^-24 of itself, 6e-5."""
+    N, d = 16 * 65535 + 35, 64
+    say(f"fp32 backward of {N} rows")
+    gen = torch.Generator(device=DEV).manual_seed(5)
+    q, v, o, g = (torch.randn((1, N, 1, d), generator=gen, device=DEV) for _ in range(4))
+    lse = torch.full((1, 1, N), 13.0, device=DEV)
+    dq, dv = kb.keyless_attention_backward(q, v, o, g, lse)
+    torch.cuda.synchronize()
+    say("fp32 backward done")
+    q, v, o, g, dq, dv = (t.view(N, d) for t in (q, v, o, g, dq, dv))
+    dd = (o.double() * g.double()).sum(1)
+    for r in (0, 33, N // 2, 16 * 65535 - 1, 16 * 65535, 16 * 65535 + 16, N - 1):
+        vr, qr, gr = v[r].double(), q[r].double(), g[r].double()
+        V = v[:r + 1].double()
+        ref = (torch.exp(V @ qr / 8 - 13) * (V @ gr - dd[r])) @ V / 8
+        assert (dq[r].double() - ref).norm() <= 1e-3 * ref.norm(), f"dQ~ {r}"
+        Q, G = q[r:].double(), g[r:].double()
+        P = torch.exp(Q @ vr / 8 - 13)
+        ref = P @ G + (P * (G @ vr - dd[r:])) @ Q / 8
+        assert (dv[r].double() - ref).norm() <= 1e-3 * ref.norm(), f"dV {r}"
+
+
 def test_unseen_rows_do_not_reach_a_row_f32(lib):
     """Causal rows before an infinite value row, and value rows after a query row
-    with a NaN gradient, get the bits that they get without it."""
+    with a NaN gradient, keep their results (a block that holds such a row is summed
+    in another order)."""
     N, H, dk = 40, 2, 64
     say("fp32 attention, non-finite rows out of sight")
     q, v, g = (synth.normal((1, N, H, dk), 34, i, 1.0, F32).to(DEV) for i in range(3))
