@@ -916,9 +916,14 @@ namespace {
 // The row sums that every call needs, and the partial sums of dV that a call with
 // these arguments uses (a workspace without room for them is accepted).
 size_t bwd_rows_bytes(int B, int N, int H) { return align256((size_t)B * H * N * sizeof(float)); }
-size_t bwd_part_bytes(int B, int N, int H, int G, int d_head, kl_dtype dtype) {
-  const int S = dtype == KL_BF16 ? kl::attn_bwd_splits(B, N, H, G) : 1;
+size_t bwd_part_bytes(int B, int N, int H, int G, int d_head, kl_dtype dtype, bool causal) {
+  const int S = dtype == KL_BF16 ? kl::attn_bwd_splits(B, N, H, G, causal) : 1;
   return S > 1 ? (size_t)S * B * N * G * d_head * sizeof(float) : 0;
+}
+// With or without the mask.
+size_t bwd_part_bytes_any(int B, int N, int H, int G, int d_head, kl_dtype dtype) {
+  return std::max(bwd_part_bytes(B, N, H, G, d_head, dtype, true),
+                  bwd_part_bytes(B, N, H, G, d_head, dtype, false));
 }
 
 }  // namespace
@@ -928,14 +933,14 @@ size_t keyless_attention_backward_workspace_size(int B, int N, int H) {
   size_t part = 0;
   for (int f = 1; (long)f * f <= H; ++f)
     if (H % f == 0)
-      for (int G : {f, H / f}) part = std::max(part, bwd_part_bytes(B, N, H, G, 128, KL_BF16));
+      for (int G : {f, H / f}) part = std::max(part, bwd_part_bytes_any(B, N, H, G, 128, KL_BF16));
   return bwd_rows_bytes(B, N, H) + align256(part);
 }
 
 size_t keyless_attention_backward_workspace_size_for(int B, int N, int H, int G, int d_head,
                                                      kl_dtype dtype) {
   if (B < 0 || N < 0 || H <= 0 || G <= 0 || H % G != 0 || d_head <= 0) return 0;
-  return bwd_rows_bytes(B, N, H) + align256(bwd_part_bytes(B, N, H, G, d_head, dtype));
+  return bwd_rows_bytes(B, N, H) + align256(bwd_part_bytes_any(B, N, H, G, d_head, dtype));
 }
 
 int keyless_attention_backward(const void* q_routed, const void* v, const void* out,
@@ -979,9 +984,9 @@ int keyless_attention_backward(const void* q_routed, const void* v, const void* 
   p.S = 1;
   if (const char* why = dtype == KL_BF16 ? kl::attn_bwd_bf16_unsupported(p) : nullptr)
     return fail(KL_ERR_UNSUPPORTED, "%s: %s", who, why);
-  const size_t part = bwd_part_bytes(B, N, H, G, d_head, dtype);
+  const size_t part = bwd_part_bytes(B, N, H, G, d_head, dtype, causal != 0);
   if (part > 0 && ws_bytes >= need + part && aligned16(ws)) {
-    p.S = kl::attn_bwd_splits(B, N, H, G);
+    p.S = kl::attn_bwd_splits(B, N, H, G, causal != 0);
     p.part = reinterpret_cast<float*>(static_cast<char*>(ws) + need);
   }
   return hip_status(kl::launch_attention_backward(p, static_cast<hipStream_t>(stream)), who);

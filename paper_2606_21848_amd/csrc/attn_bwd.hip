@@ -549,7 +549,8 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_dv_kernel(BwdParams p) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   // Groups fastest in the grid, as in the dQ~ kernel (value tile 0 is the
   // heaviest under the causal mask).
-  const int kvt = blockIdx.y, g = blockIdx.x, b = blockIdx.z % p.B, split = blockIdx.z / p.B;
+  const int kvt = blockIdx.y, g = blockIdx.x, split = p.S > 1 ? blockIdx.z / p.B : 0;
+  const int b = blockIdx.z - split * p.B;
   const int R = p.H / p.G;
   const int t = threadIdx.x, lane = t & 63;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
@@ -579,9 +580,12 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_dv_kernel(BwdParams p) {
   const int ntq = (p.N + kTileRows - 1) / kTileRows;
   const int qt0 = p.causal ? (kvt * BKVD) / kTileRows : 0;
   const int per_head = ntq - qt0;
-  // The pairs of this workgroup: its share of the splits.
-  const int first = (int)((long)R * per_head * split / p.S);
-  const int items = (int)((long)R * per_head * (split + 1) / p.S);
+  // The pairs of this workgroup: all, or its share of the splits.
+  int first = 0, items = R * per_head;
+  if (p.S > 1) {
+    first = (int)((long)items * split / p.S);
+    items = (int)((long)items * (split + 1) / p.S);
+  }
   const TileCopier<D> cp(wave, lane);
   const unsigned char* gQ = reinterpret_cast<const unsigned char*>(p.q);
   const unsigned char* gD = reinterpret_cast<const unsigned char*>(p.dout);
@@ -823,18 +827,36 @@ hipError_t launch_mfma(const BwdParams& p, hipStream_t st) {
 // fp32 partial sums. One workgroup per tile fills the chip only with many tiles;
 // a grouped layer has few, each with every head of its group to walk (12 heads on
 // 2 groups, 2 x 1000 tokens: 24 workgroups, 280 us). Three workgroups per CU even
-// out the causal tiles' lengths; a split of fewer than four pairs (ten once every
-// CU has a tile) costs more in partials than it saves, and so does any split above
-// two tiles per CU. Forward + backward at a target of 1 / 512 / 768 / 1024
+// out the causal tiles' lengths; a split of fewer than four pairs costs more in
+// partials than it saves. Forward + backward at a target of 1 / 512 / 768 / 1024
 // workgroups, us: 12 on 2 heads, 8192 tokens 2687 / 997 / 928 / 904, 2000 tokens
-// 664 / 156 / 166 / 168; 32 on 8, 6000 tokens 1655 / 1386 / 1183 / 1158. One
-// workgroup per tile / split at 32 on 32 heads: 2400 tokens (416 tiles) 260 / 243,
-// 3000 (512) 342 / 339, 3500 (608) 429 / 438, 4200 (704) 555 / 589.
-int attn_bwd_splits(int B, int N, int H, int G) {
+// 664 / 156 / 166 / 168; 32 on 8, 6000 tokens 1655 / 1386 / 1183 / 1158.
+// Two workgroups share a CU: with more than a quarter of a round of tiles (128 of 512)
+// a split has less to gain and needs more pairs. Unmasked, where the tiles are equal,
+// the splits must also fill whole rounds (two with many pairs), and three quarters of a
+// round are left whole. Over 700 shapes of 90 to 600 tiles none is slower than whole
+// tiles by 4% (80 were by more than 3%, up to 18%, when every mask took ceil(768 /
+// tiles) splits of 4 or, from 256 tiles on, 10 pairs). Backward, heads x rows, us (whole
+// / S splits; in brackets the tiles and their pairs):
+//   unmasked  64 x 500 (192, 8) 54.5 / S 2 63.1, 32 x 1000 (192, 16) 88.3 / S 2 90.5, S 4
+//             91.2, 16 x 2000 (176, 32) 156 / S 2 146, S 3 155, 32 x 2000 (352, 32) 234 / S 2
+//             231, S 3 246, 64 x 1500 (512, 24) 233 / S 2 255
+//   causal    64 x 500 53.0 / S 2 57.4, 32 x 810 (160, 13) 74.9 / S 2 71.3, S 3 65.1, 64 x
+//             1244 (448, 20) 141 / S 2 151, 32 x 2688 (448, 42) 251 / S 2 269, 32 heads on 8,
+//             4 x 2922 (512, 184) 707 / S 2 600; above 512 tiles none gain (32 x 3500 with
+//             the forward 429 / 438)
+int attn_bwd_splits(int B, int N, int H, int G, bool causal) {
   const long tiles = (long)G * B * ((N + BKVD - 1) / BKVD);
   const long pairs = (long)(H / G) * ((N + kTileRows - 1) / kTileRows);  // of the heaviest tile
-  if (tiles == 0 || tiles > 512) return 1;
-  return (int)std::max(1L, std::min((768 + tiles - 1) / tiles, pairs / (tiles < 256 ? 4 : 10)));
+  if (tiles == 0 || tiles > (causal ? 512 : 384)) return 1;
+  long S;
+  if (causal || tiles <= 128) {
+    const int least = tiles <= 128 ? 4 : tiles < 192 ? 5 : tiles < 256 ? 8 : tiles <= 384 ? 11 : 22;
+    S = std::min((768 + tiles - 1) / tiles, pairs / least);
+  } else {
+    S = std::min((tiles < 256 && pairs < 64 ? 512 : 1024) / tiles, pairs / (tiles < 256 ? 10 : 12));
+  }
+  return (int)std::max(1L, S);
 }
 
 const char* attn_bwd_bf16_unsupported(const BwdParams& p) {

@@ -242,7 +242,7 @@ struct BwdParams {
   float* part;       // their fp32 partial sums [S, B, N, G, D]
   int block0;        // first 16-row block of this launch (fp32)
 };
-int attn_bwd_splits(int B, int N, int H, int G);
+int attn_bwd_splits(int B, int N, int H, int G, bool causal);
 // nullptr when the bf16 backward takes the call, else the reason it does not.
 const char* attn_bwd_bf16_unsupported(const BwdParams& p);
 hipError_t launch_attention_backward(const BwdParams& p, hipStream_t stream);

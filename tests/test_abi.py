@@ -130,11 +130,14 @@ def test_backward_workspace_is_what_the_call_uses(lib):
             for d in (64, 128):
                 n = size_for(B, N, H, G, d, kb.KL_BF16)
                 assert rows(B, N, H) <= n <= size(B, N, H) <= rows(B, N, H) + (120 << 20)
-    # One value tile per head and more than two per CU: nothing to split.
+    # More value tiles than two per CU: nothing to split.
     assert size_for(1, 8192, 32, 32, 128, kb.KL_BF16) == rows(1, 8192, 32)
     # Two groups of 2 x 1000 tokens, 24 value tiles: the largest tile's 96 (head,
     # query tile) pairs go to 24 workgroups, each with partial sums.
     assert size_for(2, 1000, 12, 2, 128, kb.KL_BF16) == rows(2, 1000, 12) + 24 * 2 * 1000 * 2 * 128 * 4
+    # Value tiles that fill most of a round with few pairs each: whole tiles are faster.
+    for B, N, H in ((2, 500, 32), (8, 500, 8), (2, 700, 32), (4, 200, 32)):
+        assert size_for(B, N, H, H, 128, kb.KL_BF16) == rows(B, N, H)
     # The largest head count there is (a prime): no walk over all its candidates.
     assert size(1, 1, 2 ** 31 - 1) >= rows(1, 1, 2 ** 31 - 1)
     assert size_for(1, 64, 8, 3, 128, kb.KL_BF16) == size_for(1, 64, 0, 1, 128, kb.KL_BF16) == 0
