@@ -406,6 +406,12 @@ bool aligned(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0;
 }  // namespace
 
 bool attn_f32_supported(const AttnParams& p) {
+  // Up to four rows on four (64 wide: eight): one or two updates of the vector-ALU
+  // kernel, which has no merge. 8 heads, causal, us (that kernel / here): 64 wide, one
+  // row 3.4 / 4.0, eight 3.8 / 4.0, sixteen 4.5 / 4.0; 128 wide, four 5.0 / 5.5, eight 5.7 /
+  // 5.7 (unmasked 5.7 / 5.3).
+  const int few = p.D == 64 ? 8 : 4;
+  if (p.N <= few && p.Nk <= few && p.H <= 65535) return false;
   return p.dtype == KL_F32 && (p.D == 64 || p.D == 128) && p.Nk > 0 && p.q_stride % 4 == 0 &&
          p.v_stride % 4 == 0 && p.o_stride % 4 == 0 && aligned(p.q) && aligned(p.v) &&
          aligned(p.out) && aligned(p.out_f32) && (p.N + 15) / 16 <= kMaxGridY;

@@ -71,10 +71,13 @@ def test_layer_f32(lib, N, d, H, G, dk, shift):
 
 
 @pytest.mark.parametrize("causal", [True, False])
-@pytest.mark.parametrize("B,N,H,G,dk", [(1, 15, 2, 2, 64), (2, 16, 4, 2, 128), (1, 17, 3, 1, 128),
+@pytest.mark.parametrize("B,N,H,G,dk", [(2, 1, 4, 2, 64), (1, 4, 3, 1, 128), (1, 5, 2, 2, 128),
+                                        (2, 8, 2, 2, 64), (1, 9, 4, 4, 64),
+                                        (1, 15, 2, 2, 64), (2, 16, 4, 2, 128), (1, 17, 3, 1, 128),
                                         (1, 129, 2, 2, 128), (2, 250, 4, 1, 64)])
 def test_attention_f32(lib, causal, B, N, H, G, dk):
-    """Whole and ragged 16-row blocks, fewer and more of them than waves."""
+    """Whole and ragged 16-row blocks, fewer and more of them than waves; the
+    most rows that the forward leaves to the vector ALU, and one more."""
     say(f"fp32 attention B={B} N={N} H={H} G={G} dk={dk} causal={causal}")
     q, v, g = (synth.normal((B, N, n, dk), 33, i, 1.0, F32) for i, n in enumerate((H, G, H)))
     o32 = torch.empty((B, N, H, dk), dtype=F32, device=DEV)
