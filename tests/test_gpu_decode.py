@@ -46,6 +46,30 @@ def _paged(cache_cpu, lengths, bs, seed):
     return data, table
 
 
+def _roomy(data, table=None, rows=8192):
+    """The cache with a capacity of `rows` rows on the GPU, past what one workgroup per
+    pair decodes: a contiguous one followed by NaN rows, a paged one with its table
+    followed by entries of the poison block (the last one)."""
+    if table is not None:
+        wide = torch.full((table.shape[0], rows // data.shape[2]), data.shape[0] - 1,
+                          dtype=torch.int32)
+        wide[:, :table.shape[1]] = table
+        return kb.ValueCache(data.to(DEV), wide.to(DEV))
+    B, G, L, d = data.shape
+    big = torch.full((B, G, rows, d), float("nan"), dtype=data.dtype, device=DEV)
+    big[:, :, :L] = data.to(DEV)
+    return kb.ValueCache(big)
+
+
+def _unused_workspace(vc, B, H):
+    """A workspace of NaN bytes: what a call leaves in it shows whether it merged."""
+    return torch.full((kb.decode_workspace_bytes(vc, B, H),), 0xFF, dtype=torch.uint8, device=DEV)
+
+
+def _assert_merged(ws):
+    assert bool((ws != 0xFF).any()), "no partial was written: the call did not split its pairs"
+
+
 CASES = [
     # dtype, d_head, H, G
     (torch.bfloat16, 128, 8, 8),
@@ -93,6 +117,14 @@ def test_decode_matches_oracle(lib, dtype, d, H, G, paged):
         assert_parity(out, ref, dtype, f"chunk={chunk}")
         zero = lengths == 0
         assert torch.all(out.cpu()[zero] == 0)
+    # The same rows in a larger capacity: the balanced split.
+    vc = _roomy(data, table) if paged else _roomy(cache)
+    ws = _unused_workspace(vc, B, H)
+    out = kb.keyless_decode(q.to(DEV), vc, lengths.to(DEV), workspace=ws)
+    torch.cuda.synchronize()
+    assert_parity(out, ref, dtype, "balanced")
+    assert torch.all(out.cpu()[lengths == 0] == 0)
+    _assert_merged(ws)
 
 
 def test_paged_equals_contiguous_bitwise(lib):
@@ -152,6 +184,32 @@ def test_balanced_mode_ragged_and_empty(lib, H, G, d, dtype):
         torch.cuda.synchronize()
         assert_parity(out, ref, dtype, f"balanced call {rep}")
         assert torch.all(out.cpu()[lengths == 0] == 0)
+    _assert_merged(ws)
+
+
+@pytest.mark.parametrize("B", [6, 70])
+@pytest.mark.parametrize("H,G", [(2, 2), (12, 2), (16, 1), (32, 1)])
+def test_balanced_contiguous_ragged(lib, B, H, G):
+    """The balanced split of a contiguous cache whose lengths differ: few pairs (one
+    wide workgroup per CU with grouped heads) and more than 64 (two of 4 waves); one
+    sequence of 5990 rows, the others up to 300, an empty one last."""
+    d, cap = 128, 6000
+    say(f"balanced contiguous B={B} H={H} G={G}")
+    rows = synth.normal((B, G, 300, d), 27, B)
+    long = synth.normal((1, G, 5990, d), 27, B + 1)
+    q = synth.normal((B, H, d), 27, B + 2)
+    lengths = synth.uniform_int(B, 0, 300, 27, B + 3).to(torch.int32)
+    lengths[0], lengths[1], lengths[-1] = 300, 5990, 0
+    vc = _roomy(rows, rows=cap)
+    vc.data[1:2, :, :5990] = long.to(DEV)
+    ws = _unused_workspace(vc, B, H)
+    out = kb.keyless_decode(q.to(DEV), vc, lengths.to(DEV), workspace=ws)
+    torch.cuda.synchronize()
+    ref = K.keyless_decode(to64(q), to64(rows), lengths.clamp(max=300).numpy(), H, G)
+    ref[1:2] = K.keyless_decode(to64(q[1:2]), to64(long), [5990], H, G)
+    assert_parity(out, ref, torch.bfloat16, "balanced contiguous")
+    assert torch.all(out.cpu()[lengths == 0] == 0)
+    _assert_merged(ws)
 
 
 @pytest.mark.parametrize("B", [63, 64, 65, 300, 1100])
@@ -162,8 +220,9 @@ def test_balanced_mode_sequence_counts(lib, B, H, G, d, dtype, paged):
     sequences the decode and merge kernels derive the work split from the
     lengths, with more the plan kernel writes it (1100 sequences also cross its
     1024-sequence scan blocks). Ragged lengths with the edge cases, and empty
-    sequences first, inside and last. A contiguous cache takes the balanced split
-    only below one (sequence, group) pair per compute unit."""
+    sequences first, inside and last, in caches of 8192 rows (little capacity per
+    pair is one workgroup without a merge). A contiguous cache takes the balanced
+    split only below one (sequence, group) pair per compute unit."""
     if not paged and B * G >= 256:
         pytest.skip("a contiguous cache with this many pairs takes one workgroup per pair")
     L = 200
@@ -176,45 +235,55 @@ def test_balanced_mode_sequence_counts(lib, B, H, G, d, dtype, paged):
     q = synth.normal((B, H, d), 19, B + 1, 1.0, dtype)
     if paged:
         data, table = _paged(cache, lengths, 16, 7)
-        vc = kb.ValueCache(data.to(DEV), table.to(DEV))
+        vc = _roomy(data, table)
         ref = K.keyless_decode(to64(q), to64(data), lengths.numpy(), H, G,
                                block_table=table.numpy(), block_size=16)
     else:
-        vc = kb.ValueCache(cache.to(DEV))
+        vc = _roomy(cache)
         ref = K.keyless_decode(to64(q), to64(cache), lengths.numpy(), H, G)
-    ws = torch.full((kb.decode_workspace_bytes(vc, B, H),), 0xFF, dtype=torch.uint8, device=DEV)
+    ws = _unused_workspace(vc, B, H)
     out = kb.keyless_decode(q.to(DEV), vc, lengths.to(DEV), workspace=ws)
     torch.cuda.synchronize()
     assert_parity(out, ref, dtype, f"balanced B={B}")
     assert torch.all(out.cpu()[lengths == 0] == 0)
+    _assert_merged(ws)
 
 
-@pytest.mark.parametrize("B", [64, 65, 300])
-def test_decode_append_balanced_sequence_counts(lib, B):
+@pytest.mark.parametrize("paged", [True, False])
+@pytest.mark.parametrize("B", [30, 64, 65, 300])
+def test_decode_append_balanced_sequence_counts(lib, B, paged):
     """The fused step (new row appended at lengths_before, decode over one more
     row) in the balanced split on both sides of the in-kernel plan's limit, whose
-    tile counts include every sequence's new row; ragged positions, paged cache.
-    Outputs against the oracle's append then decode, the cache bit-equal to the
+    tile counts include every sequence's new row, with 30 sequences (60 pairs) on
+    wide workgroups; ragged positions in caches of 8192 rows. Outputs against the oracle's append then decode, the cache bit-equal to the
     oracle's append afterwards."""
     H, G, d, L, dtype = 4, 2, 128, 96, torch.bfloat16
-    say(f"decode_append balanced B={B}")
+    if not paged and B * G >= 256:
+        pytest.skip("a contiguous cache with this many pairs takes one workgroup per pair")
+    say(f"decode_append balanced B={B} paged={paged}")
     cache = synth.normal((B, G, L, d), 21, B, 1.0, dtype)
     vnew = synth.normal((B, G, d), 21, B + 1, 1.0, dtype)
     q = synth.normal((B, H, d), 21, B + 2, 1.0, dtype)
-    data, table = _paged(cache, torch.full((B,), L, dtype=torch.int32), 16, 8)
-    tab = table.numpy()
     before = synth.uniform_int(B, 0, L - 1, 21, B + 3).to(torch.int32)
     before[0] = 0
     before[-1] = L - 1
-    ref_data = K.value_cache_append(to64(data), to64(vnew[:, None]), before.tolist(), tab, 16)
-    ref = K.keyless_decode(to64(q), ref_data, (before + 1).numpy(), H, G, block_table=tab,
-                           block_size=16)
-    dev_data = data.to(DEV)
-    vc = kb.ValueCache(dev_data, table.to(DEV))
-    out = kb.keyless_decode_append(q.to(DEV), vnew.to(DEV), vc, before.to(DEV))
+    if paged:
+        data, table = _paged(cache, torch.full((B,), L, dtype=torch.int32), 16, 8)
+        where = dict(block_table=table.numpy(), block_size=16)
+        vc = _roomy(data, table)
+    else:
+        data, where = cache, {}
+        vc = _roomy(cache)
+    ref_data = K.value_cache_append(to64(data), to64(vnew[:, None]), before.tolist(),
+                                    *where.values())
+    ref = K.keyless_decode(to64(q), ref_data, (before + 1).numpy(), H, G, **where)
+    ws = _unused_workspace(vc, B, H)
+    out = kb.keyless_decode_append(q.to(DEV), vnew.to(DEV), vc, before.to(DEV), workspace=ws)
     torch.cuda.synchronize()
     assert_parity(out, ref, dtype, f"fused step, balanced B={B}")
-    assert np.array_equal(to64(dev_data.cpu()), ref_data, equal_nan=True)
+    got = vc.data if paged else vc.data[:, :, :L]
+    assert np.array_equal(to64(got.cpu()), ref_data, equal_nan=True)
+    _assert_merged(ws)
 
 
 def test_lengths_beyond_capacity_are_clamped(lib):
@@ -552,8 +621,8 @@ def test_long_context_most_splits(lib, H, G):
 @pytest.mark.parametrize("paged", [False, True])
 def test_wide_workgroups(lib, dtype, B, H, G, d, L, paged):
     """Each number of waves of the wide workgroups (one split, and fixed splits),
-    lengths from empty to full, as a decode and as a fused step (bit-equal to append
-    then decode, whose new row joins the same way)."""
+    lengths from empty to full, as a decode and as a fused step, whose cache is bit-equal
+    to the one that the append call leaves."""
     if paged:
         L = -(-L // 16) * 16
     say(f"wide decode {dtype} B={B} H={H} G={G} d={d} L={L} paged={paged}")

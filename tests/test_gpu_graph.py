@@ -28,15 +28,16 @@ def _capture(fn):
 
 
 def test_latent_decode_graph_replays(lib):
-    B, H, G, dk, r, L = 6, 32, 1, 128, 128, 700
+    B, H, G, dk, r, L = 6, 32, 1, 128, 128, 6000  # the balanced split, with its merge
     say("graph: latent decode")
     cache = synth.normal((B, G, L, r), 61, 1).to(DEV)
     W_post = synth.normal((H, r, dk), 61, 3, dk ** -0.5).to(DEV)
-    lengths = torch.tensor([700, 1, 0, 333, 16, 512], dtype=torch.int32, device=DEV)
+    lengths = torch.tensor([6000, 1, 0, 333, 16, 512], dtype=torch.int32, device=DEV)
     vc = kb.ValueCache(cache)
     q = torch.empty((B, H, dk), dtype=torch.bfloat16, device=DEV)
     out = torch.empty_like(q)
-    ws = torch.empty(kb.latent_decode_workspace_bytes(vc, B, H, dk), dtype=torch.uint8, device=DEV)
+    ws = torch.full((kb.latent_decode_workspace_bytes(vc, B, H, dk),), 0xFF, dtype=torch.uint8,
+                    device=DEV)
     q.copy_(synth.normal((B, H, dk), 61, 2).to(DEV))
     g = _capture(lambda: kb.keyless_latent_decode(q, W_post, vc, lengths, out=out, workspace=ws))
     for rep in range(4):
@@ -47,13 +48,15 @@ def test_latent_decode_graph_replays(lib):
         g.replay()
         torch.cuda.synchronize()
         assert torch.equal(out, ref), f"replay {rep}"
+    # Past the absorbed queries and the outputs lie the decode's partials.
+    assert bool((ws[-kb.decode_workspace_bytes(vc, B, H):] != 0xFF).any())
 
 
 def test_decode_step_graph_replays(lib):
     """The decode step of a layer (projections with append, then the balanced
     decode with its plan and merge) captured once, replayed on a cache that the
     eager reference rebuilds before every replay."""
-    B, d, H, G, dk, L = 4, 512, 8, 2, 128, 300
+    B, d, H, G, dk, L = 6, 512, 8, 2, 128, 2100
     say("graph: project + decode")
     W_Q = synth.normal((d, H * dk), 62, 1, d ** -0.5).to(DEV)
     W_R = synth.normal((H, dk, dk), 62, 2, dk ** -0.5).to(DEV)
@@ -62,11 +65,11 @@ def test_decode_step_graph_replays(lib):
     base = synth.normal((B, G, L, dk), 62, 4).to(DEV)
     cache = base.clone()
     vc = kb.ValueCache(cache)
-    before = torch.tensor([0, 100, 299, 17], dtype=torch.int32, device=DEV)
+    before = torch.tensor([0, 100, 2099, 17, 300, 1500], dtype=torch.int32, device=DEV)
     x = torch.empty((B, d), dtype=torch.bfloat16, device=DEV)
     q = torch.empty((B, H, dk), dtype=torch.bfloat16, device=DEV)
     out = torch.empty_like(q)
-    ws = torch.empty(max(kb.decode_workspace_bytes(vc, B, H), 256), dtype=torch.uint8, device=DEV)
+    ws = torch.full((kb.decode_workspace_bytes(vc, B, H),), 0xFF, dtype=torch.uint8, device=DEV)
 
     def step():
         kb.keyless_decode_project(x, packed, H, G, cache=vc, lengths_before=before, q_routed_out=q)
@@ -86,3 +89,4 @@ def test_decode_step_graph_replays(lib):
         assert torch.equal(q, rq), f"replay {rep}: routed queries"
         assert torch.equal(cache, ref_cache), f"replay {rep}: cache"
         assert torch.equal(out, ref), f"replay {rep}: output"
+    assert bool((ws != 0xFF).any()), "no partial was written: the decode did not merge"

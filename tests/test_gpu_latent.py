@@ -8,7 +8,7 @@ import torch
 from oracle import keyless as K
 from paper_2606_21848_amd import binding as kb
 from tests.parity import assert_parity, say, to64
-from tests.test_gpu_decode import _lengths, _paged
+from tests.test_gpu_decode import _lengths, _paged, _roomy
 from workloads import configs, synth
 
 pytestmark = pytest.mark.gpu
@@ -49,6 +49,14 @@ def test_latent_decode_matches_oracle(lib, dtype, dk, r, H, G, paged):
     torch.cuda.synchronize()
     assert_parity(out, ref, dtype, "latent decode")
     assert torch.all(out.cpu()[lengths == 0] == 0)
+    # The same rows in a larger capacity: the balanced split and its merge.
+    vc = _roomy(data, table) if paged else _roomy(cache)
+    ws = torch.full((kb.latent_decode_workspace_bytes(vc, B, H, dk),), 0xFF, dtype=torch.uint8,
+                    device=DEV)
+    out = kb.keyless_latent_decode(q.to(DEV), W_post.to(DEV), vc, lengths.to(DEV), workspace=ws)
+    torch.cuda.synchronize()
+    assert_parity(out, ref, dtype, "latent decode, balanced")
+    assert bool((ws[-kb.decode_workspace_bytes(vc, B, H):] != 0xFF).any())
 
 
 def test_latent_decode_explicit_scale_and_reused_workspace(lib):

@@ -33,9 +33,9 @@ def _paged(cache, block_size, seed):
 @pytest.mark.parametrize("paged", [False, True])
 def test_noalloc_decode_matches_workspace_decode(lib, paged):
     H, G, d = 32, 8, 128
-    # First call: 24 sequences (192 pairs, the balanced split with merges);
-    # second, smaller: 3 sequences (fixed splits over the capacity).
-    for call, (B, L, seed) in enumerate([(24, 3008, 31), (3, 2048, 32)]):
+    # First call: 20 sequences (160 pairs of more than 768 KiB, the balanced split with
+    # merges); second, smaller: 3 sequences (fixed splits over the capacity).
+    for call, (B, L, seed) in enumerate([(20, 3120, 31), (3, 2048, 32)]):
         say(f"noalloc decode call {call} B={B} L={L} paged={paged}")
         cache = synth.normal((B, G, L, d), seed, 1, 1.0, torch.bfloat16)
         q = synth.normal((B, H, d), seed, 2, 1.0, torch.bfloat16)
@@ -49,9 +49,11 @@ def test_noalloc_decode_matches_workspace_decode(lib, paged):
         else:
             vc = kb.ValueCache(cache.to(DEV))
             ref = K.keyless_decode(to64(q), to64(cache), lengths.numpy(), H, G)
-        assert kb.decode_workspace_bytes(vc, B, H) > 0, "this case must use a workspace"
         qd, ld = q.to(DEV), lengths.to(DEV)
-        want = kb.keyless_decode(qd, vc, ld)
+        ws = torch.full((kb.decode_workspace_bytes(vc, B, H),), 0xFF, dtype=torch.uint8, device=DEV)
+        want = kb.keyless_decode(qd, vc, ld, workspace=ws)
+        torch.cuda.synchronize()
+        assert bool((ws != 0xFF).any()), "this case must write partials into a workspace"
         got = kb.keyless_decode_noalloc(qd, vc, ld,
                                         out=torch.full_like(qd, float("nan")))
         torch.cuda.synchronize()
