@@ -1089,7 +1089,7 @@ def extra_measurements(torch, kb, configs, dev):
         "graph_ms": round(st_g["median_ms"], 4), "graph_stats": st_g,
         "graph_tokens_per_s": rate(st_g, la["B"], 1.0),
         "graph_cache_gbps": rate(st_g, lbytes, 1e-9),
-        "note": "ms: eager calls back to back (five kernels per call); graph_ms: the same call "
+        "note": "ms: eager calls back to back (four kernels per call); graph_ms: the same call "
                 "replayed from a captured HIP graph",
         "cpu_baseline": cpu_entry(round(nb / el, 2), "tokens/s", cores,
                                   f"{nb} sequences (all 32 heads) in {el:.1f} s")}

@@ -1,8 +1,8 @@
 // Vector-ALU keyless attention (fp32 arithmetic), for what the matrix-core
 // kernels do not take: no value rows, a few fp32 rows, fp32 operands that are
-// not 16-byte aligned, strides past their limits. A flash-style kernel where one LDS tile
-// of values serves both the scores (Eq. 4) and the weighted sum, 16 lanes per
-// query row.
+// not 16-byte aligned, strides past their limits. A flash-style kernel where one
+// LDS tile of values serves both the scores (Eq. 4) and the weighted sum, 16
+// lanes per query row.
 
 #include "kl_device.h"
 #include "kl_internal.h"

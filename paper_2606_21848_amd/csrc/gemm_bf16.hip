@@ -357,7 +357,12 @@ hipError_t launch_gemm_bf16(const GemmBf16Args& a, hipStream_t st) {
   // 128 tiles 0.95 per round of 512 (two per CU) or 0.65 for a last one of at
   // most 256; 64 x 64 tiles 0.15 + 0.22 per 256. At N 1792, K 1536 (256 / 128 /
   // 64, us): M 517: 37 / 18 / 9.3; M 2000: 38 / 17 / 23; M 4096: 40 / 28 / 41;
-  // at N = 8192, K = 4096: M 1000: 83 / 62 / 100, M 8192: 422 / 470 / 778.
+  // at N = 8192, K = 4096: M 1000: 83 / 62 / 100, M 8192: 422 / 470 / 778. The number
+  // of k-steps cancels as long as they outweigh a tile's entry and store: over 771
+  // shapes (K 64 to 8192) no choice is slower than 256-wide tiles by 2.5%, but with one to
+  // four k-steps the fastest shape is up to 30% faster (M 3000, N 3072, K 256: 14 / 16 /
+  // 18 for 64 / 128 / 256), and so are one-k-loop batches of 128 x 128 outputs (96 items
+  // over K 2048: 20 on 128-wide tiles, 39 on the 64-wide ones that are taken).
   auto rounds = [](double t, double per, double full, double part, double few) {
     const double whole = std::floor(t / per), rest = t - whole * per;
     return whole * full + (rest == 0 ? 0. : (2 * rest <= per ? few : part));

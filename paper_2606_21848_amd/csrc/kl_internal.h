@@ -95,7 +95,7 @@ struct ProjectParams {
 bool project_supported(int K);
 hipError_t launch_project(const ProjectParams& p, hipStream_t stream);
 
-// C[b] (M x N) = A[b] (M x K) B[b] (K x N) [+ A1 B1] [+ C], fp32 arithmetic on
+// C[b] (M x N) = A[b] (M x K) B[b] (K x N) [+ A1 B1], fp32 arithmetic on
 // fp32 or bf16 elements, row-major C. Element (m, k) of A is at m lda + k a_cs,
 // element (k, n) of B at k ldb + n b_cs (a_cs, b_cs of 0 mean 1), so transposed
 // operands are a choice of strides; no alignment is needed. Optional: a second
