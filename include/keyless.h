@@ -343,10 +343,10 @@ int keyless_decode_project(const void* x, const void* packed, int B, int d_model
  *            Calls that run at the same time must not share it.
  * Each cached value tile is read from HBM once and used both for the scores
  * and for the weighted sum. Work split (the built-in choice): a contiguous
- * cache with at least 256 (b, group) pairs, or one with little cache per pair
- * (256 KiB to 1 MiB, by the number of pairs), gets one workgroup per pair and no
- * merge; at most 4 sequences get fixed splits; otherwise a fixed set of 512 (or 256
- * larger) workgroups shares the 16-row tiles of
+ * cache with at least 256 (b, group) pairs, and any cache of little capacity per
+ * pair (256 KiB to 1 MiB, by the number of pairs), gets one workgroup per pair and
+ * no merge; at most 4 sequences get fixed splits; otherwise a fixed set of 512 (or
+ * 256 larger) workgroups shares the 16-row tiles of
  * all pairs evenly (a plan kernel prefix-sums the lengths on the device), and
  * a merge kernel combines the pairs that several workgroups shared, always in
  * the same order, so results are reproducible for fixed inputs. The workspace
