@@ -25,7 +25,10 @@
  *    the host (that would need a synchronisation). The kernels clamp a length
  *    to [0, capacity], treat block ids outside [0, num_blocks) as empty rows,
  *    and drop appended rows that fall beyond capacity, so bad device data can
- *    give wrong results but never an out-of-bounds access.
+ *    give wrong results but never an out-of-bounds access. A call's kernels read
+ *    the lengths several times and derive their work split from them: they must
+ *    not change until the call has run on its stream (data written on another
+ *    stream needs an event or a synchronisation before the call).
  *  - Supported: d_head in {64, 128}; H / G any value for prefill, 1 to 8 for
  *    decode (also 16 or 32 for a bf16 cache with d_head 128); element type bf16
  *    (stored as raw 16-bit words) or fp32; arithmetic is fp32 in both cases.
